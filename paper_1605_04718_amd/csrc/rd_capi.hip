@@ -71,7 +71,7 @@ long tune_key(int dev, int n, int prec)
 // In host code `scratch` names a host-side stand-in: its device address is
 // taken once per device with hipGetSymbolAddress and used from then on.
 constexpr size_t kNoAllocHeader = 256;
-constexpr size_t kNoAllocSlots = (size_t)96 << 20;  // 96 MiB of solve slots
+constexpr size_t kNoAllocSlots = (size_t)128 << 20;  // 128 MiB of solve slots
 static __device__ __align__(256) unsigned char scratch[kNoAllocHeader + kNoAllocSlots];
 
 namespace {

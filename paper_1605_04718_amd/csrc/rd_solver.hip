@@ -1144,6 +1144,12 @@ __global__ __launch_bounds__(N *N / R) void k_solve_streamed(SolveArgs a)
     }
 }
 
+}  // namespace rd
+
+#include "rd_pcg.hpp"
+
+namespace rd {
+
 // Uneven batches: one persistent launch of T-thread workgroups serves items
 // of every grid class.  Each class runs the strip layout that T threads give
 // it (R = n^2 / T cells per thread): resident where its arrays fit the VGPR
@@ -2270,17 +2276,17 @@ hipError_t launch_fill_u32(unsigned *p, unsigned v, int count, hipStream_t s)
 // fit the VGPR budget of the workgroup size.
 namespace {
 
-enum Kind { kNone, kResident, kStreamed, kCoop };
+enum Kind { kNone, kResident, kStreamed, kCoop, kSpectral };
 
 Kind tile_kind(int n, int precision, int cpt)
 {
     if (precision == 0) {
         if (n == 32 && (cpt == 4 || cpt == 8 || cpt == 16))
             return kResident;
-        if (n == 64 && (cpt == 4 || cpt == 8 || cpt == 16))
-            return kResident;
-        if (n == 128 && (cpt == 16 || cpt == 32))
-            return kResident;
+        // one kernel serves every tile of these two sizes
+        if ((n == 64 && (cpt == 4 || cpt == 8 || cpt == 16)) ||
+            (n == 128 && (cpt == 16 || cpt == 32)))
+            return kSpectral;
         if (n == 256 && cpt == kCoopR)
             return kCoop;
         if (n == 256 && (cpt == 64 || cpt == 128))
@@ -2319,15 +2325,19 @@ bool tile_supported(int n, int precision, int cpt)
     return tile_kind(n, precision, cpt) != kNone;
 }
 
-// Defaults measured by rd_autotune on MI355X (40-step trial solves): in FP32
-// 16 cells per thread wins at every resident size (64, 256 and 1024-thread
-// workgroups at 32^2, 64^2 and 128^2).  At 256^2 in FP32 the cooperative
+// Defaults measured on MI355X.  FP32 64^2 and 128^2: the spectrally
+// preconditioned kernel (rd_pcg.hpp) at every problem size and tolerance: per
+// IMEX step of one item 48 us against 90 us for plain CG (512 items of 128^2
+// near the posterior, first 500 steps), 52 against 196 us (4096 prior draws,
+// first 200 steps, where plain CG takes 51 iterations per step and this
+// kernel 3), 42 against 111 us for a single item, and 2000 prior draws at
+// 64^2 in 32 against 75 ms.  At 32^2 16 cells per thread.  At 256^2 in FP32 the cooperative
 // tile (16 cells per thread, four workgroups per item) is 9 to 14 times
 // faster per item than the streamed one.
 int default_cpt(int n, int precision)
 {
     if (precision == 0)
-        return n == 32 ? 16 : n == 64 ? 16 : n == 128 ? 16 : n == 256 ? kCoopR : 0;
+        return n == 32 ? 16 : n == 64 ? 16 : n == 128 ? 32 : n == 256 ? kCoopR : 0;
     return n == 32 ? 8 : n == 64 ? 16 : n == 128 ? 32 : n == 256 ? 128 : 0;
 }
 
@@ -2335,6 +2345,8 @@ size_t solve_slot_bytes(int n, int precision, int cpt)
 {
     if (tile_kind(n, precision, cpt) == kCoop)  // one member's strip: 4 arrays
         return (size_t)4 * kCoopStrip * kCoopN * sizeof(float);
+    if (tile_kind(n, precision, cpt) == kSpectral)
+        return n == 64 ? pcg::slot_bytes<64>() : pcg::slot_bytes<128>();
     // SlotLayout: low parts and two increments per species (6 arrays), and
     // for streamed tiles the strip arrays and p after them (6 more)
     const size_t arrays = tile_kind(n, precision, cpt) == kStreamed ? 12 : 6;
@@ -2360,10 +2372,11 @@ int solve_wgs_per_cu(int n, int precision, int cpt)
         return occupancy(k_solve_streamed<NN, RR, T>, NN * NN / RR);
     if (tile_kind(n, precision, cpt) == kCoop)
         return occupancy(k_solve_coop, kCoopThreads);
+    if (tile_kind(n, precision, cpt) == kSpectral)
+        return n == 64 ? occupancy(pcg::k_solve_pcg<64>, pcg::Layout<64>::T)
+                       : occupancy(pcg::k_solve_pcg<128>, pcg::Layout<128>::T);
     if (precision == 0) {
         RD_OCC_R(32, 4, float) RD_OCC_R(32, 8, float) RD_OCC_R(32, 16, float)
-        RD_OCC_R(64, 4, float) RD_OCC_R(64, 8, float) RD_OCC_R(64, 16, float)
-        RD_OCC_R(128, 16, float) RD_OCC_R(128, 32, float)
         RD_OCC_S(256, 64, float) RD_OCC_S(256, 128, float)
     } else {
         RD_OCC_R(32, 4, double) RD_OCC_R(32, 8, double) RD_OCC_R(32, 16, double)
@@ -2495,10 +2508,15 @@ hipError_t launch_solve(int n, int precision, TileChoice tile, const SolveArgs &
         return go_streamed<NN, RR, T>(a, wgs, s);
     if (tile_kind(n, precision, cpt) == kCoop)
         return launch_solve_coop(a, wgs, s);
+    if (tile_kind(n, precision, cpt) == kSpectral) {
+        if (n == 64)
+            hipLaunchKernelGGL(pcg::k_solve_pcg<64>, dim3(wgs), dim3(pcg::Layout<64>::T), 0, s, a);
+        else
+            hipLaunchKernelGGL(pcg::k_solve_pcg<128>, dim3(wgs), dim3(pcg::Layout<128>::T), 0, s, a);
+        return hipGetLastError();
+    }
     if (precision == 0) {
         RD_RES(32, 4, float) RD_RES(32, 8, float) RD_RES(32, 16, float)
-        RD_RES(64, 4, float) RD_RES(64, 8, float) RD_RES(64, 16, float)
-        RD_RES(128, 16, float) RD_RES(128, 32, float)
         RD_STR(256, 64, float) RD_STR(256, 128, float)
     } else {
         RD_RES(32, 4, double) RD_RES(32, 8, double) RD_RES(32, 16, double)
