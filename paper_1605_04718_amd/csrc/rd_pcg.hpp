@@ -1,4 +1,6 @@
-// Resident FP32 solve with a spectral preconditioner (64 x 64 and 128 x 128).
+// Solves with a spectral preconditioner: one workgroup per item at 32 x 32,
+// 64 x 64 and 128 x 128, a group of four workgroups at 256 x 256, in FP32 and
+// FP64.
 //
 // The increment systems (sigma + c L) d = r0 of a time step (L the 5-point
 // Neumann Laplacian times h^2, sigma = 1/dt + e(x)) differ from their
@@ -13,22 +15,29 @@
 // matrix cores in FP16 with FP32 accumulation: a preconditioner only chooses
 // the search direction, and its FP16 rounding (2^-11 relative) limits the
 // contraction per iteration to about 0.05, not the accuracy of the solve.
-// Residuals, increments and the operator stay FP32, dot products, step
-// lengths and the stopping test FP64, and the fields FP64.
+// The iteration's vectors and operator are FP32, its dot products, step
+// lengths and stopping test FP64; residuals are evaluated in FP64 from FP64
+// fields.  FP32 problems take the increment that this gives.  FP64 problems
+// add it to an FP64 field, evaluate the residual of the implicit system for
+// that field in FP64, and solve for a further correction until that true
+// residual meets the tolerance (iterative refinement; the tolerance then
+// bounds the evaluated residual, not a recursively updated one).
 //
-// Layout: one workgroup of W = N / 16 waves per item; wave w owns rows
-// 16 w .. 16 w + 15, lane l the C = N / 64 columns C l .. C l + C - 1 of each
-// (R = 16 C cells per thread).  Vertical neighbours are the thread's own
+// Layout: strip s of an item is K whole rows, lane l of it the C columns
+// C l .. C l + C - 1 (R = K C cells per thread).  A wave is one strip, at
+// 32 x 32 two.  Vertical neighbours are the thread's own
 // registers, horizontal ones a DPP lane shift, so a stencil pass reads no
 // LDS; only the rows above and below a wave's strip come from another wave.
 //
 // Global slot of a workgroup: the fields X_u, X_v in FP64, then the last two
 // increments of each species in FP32.
 //
-// What bounds it (128 x 128, cycles of a 120 k-cycle IMEX step near the
-// posterior): the passes over the slot's fields and increments (residuals
-// 28 k, predictor 52 k, fold 13 k; 1.3 MB per step from L2 and the memory-side
-// cache, 7 TB/s over the chip), not the transforms (10 k per application).
+// What bounds it: issue of vector instructions (128 x 128: 2 000 per wave for
+// the set-up of a system, 1 800 per iteration, two waves per SIMD), and with
+// every CU busy also the passes over the slot (1.15 MB per IMEX step from L2
+// and the memory-side cache, 7 TB/s over the chip).  512 items of 128 x 128
+// near the posterior, 500 steps: 42.8 ms, plain CG 89.5; 64 FP64 items, 40
+// steps: 4.3 ms, plain CG with streamed arrays 144.
 #pragma once
 
 namespace rd {
@@ -38,7 +47,30 @@ typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kRows = 16;  // rows per wave: one matrix-core tile
+// N x N cells, W waves per workgroup, K rows per strip, G workgroups per item.
+template <int N_, int W_, int K_, int G_>
+struct Shape {
+    static constexpr int N = N_, W = W_, K = K_, G = G_;
+    static constexpr int LW = N < 64 ? N : 64;    // lanes of a strip
+    static constexpr int C = N / LW;              // columns per lane
+    static constexpr int R = K * C;               // cells per thread
+    static constexpr int T = 64 * W;              // threads per workgroup
+    static constexpr int M = N / G;               // rows of one workgroup
+    static constexpr int ST = M / K;              // strips of one workgroup
+    static constexpr int KS = N / 32;             // 32-wide slices of a contraction
+    static constexpr int NT = N / 16;             // 16-row tiles of a table
+    static constexpr int SN = N + 8;              // stride of the FP16 row buffers
+    static constexpr int ZN = N + 4;              // stride of the FP32 rows of z
+    static constexpr int cells = M * N;           // cells of one workgroup
+    static_assert(ST * LW == T, "strips cover the workgroup");
+};
+// 32^2: two waves of 2 x 8 rows take 9.9 us per step for one item and 26.8 for
+// 2000; one wave of 2 x 16 rows 13.5 and 26.4, four of 2 x 4 rows 8.8 and
+// 33.5.  128^2: eight waves of 16 rows 43 ms for 512 items of 500 steps;
+// sixteen of 8 rows, whose 128 registers do not hold a strip, 64.
+using S32 = Shape<32, 2, 8, 1>;
+using S64 = Shape<64, 4, 16, 1>;
+using S128 = Shape<128, 8, 16, 1>;
 
 // Reduction slots (FP64, W each): the predictor's 8 sums, then |r|^2, r.z,
 // p.q and the misfit or step size.  No two consecutive reductions share one.
@@ -48,29 +80,18 @@ struct RedSlots {
                          total = 12 * W;
 };
 
-template <int N>
-struct Layout {
-    static constexpr int C = N / 64;      // columns per lane
-    static constexpr int W = N / kRows;   // waves per item
-    static constexpr int T = 64 * W;      // threads per item
-    static constexpr int R = kRows * C;   // cells per thread
-    static constexpr int KS = N / 32;     // 32-wide slices of a contraction
-    static constexpr int SN = N + 8;      // stride of the FP16 row buffers
-    static constexpr int ZN = N + 4;      // stride of the FP32 rows of z
-};
-
 // LDS of a workgroup.  qf / qt: Q and Q^T as matrix-core fragments (tile of
 // 16 rows, 32-wide slice, lane, 8 values: a fragment is one conflict-free
 // 16-byte read).  x, y: the FP16 arrays of the transform stages, padded so
 // that the 16 rows a fragment touches start in different banks.
-template <int N>
+template <class S>
 struct Lds {
-    _Float16 qf[N * N];
-    _Float16 qt[N * N];
-    _Float16 x[N * Layout<N>::SN];
-    _Float16 y[N * Layout<N>::SN];
-    float lam[N];  // 2 - 2 cos(pi k / N)
-    double red[RedSlots<Layout<N>::W>::total];
+    _Float16 qf[S::N * S::N];
+    _Float16 qt[S::N * S::N];
+    _Float16 x[S::N * S::SN];
+    _Float16 y[S::N * S::SN];
+    float lam[S::N];  // 2 - 2 cos(pi k / N)
+    double red[RedSlots<S::W>::total];
     int item;
 };
 
@@ -91,12 +112,51 @@ __device__ __forceinline__ void group_end()
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// An offset whose use the compiler cannot hoist: otherwise the per-row
-// addresses of every global array stay live through the time loop.
-__device__ __forceinline__ int opaque(int o)
+// Values whose use the compiler cannot hoist: otherwise the per-row addresses
+// of every global array stay live through the time loop.
+__device__ __forceinline__ unsigned opaque(unsigned o)
 {
     asm volatile("" : "+v"(o));
     return o;
+}
+template <typename T>
+__device__ __forceinline__ T *opaque(T *p)
+{
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
+// C neighbouring values at a 32-bit lane offset (in values) from a
+// wave-uniform row pointer: one access of up to 16 bytes whose address is the
+// scalar row pointer plus the one lane offset.
+template <int C, typename T>
+__device__ __forceinline__ void load_cols(const T *row, unsigned off, T (&v)[C])
+{
+    constexpr int V = C * sizeof(T) > 16 ? 16 / sizeof(T) : C;
+    typedef T vec __attribute__((ext_vector_type(V)));
+    typedef __attribute__((address_space(1))) vec gvec;  // (global, not flat)
+#pragma unroll
+    for (int c = 0; c < C; c += V) {
+        const vec t = *(const gvec *)((const char *)(row + c) + off * (unsigned)sizeof(T));
+#pragma unroll
+        for (int j = 0; j < V; ++j)
+            v[c + j] = t[j];
+    }
+}
+template <int C, typename T>
+__device__ __forceinline__ void store_cols(T *row, unsigned off, const T (&v)[C])
+{
+    constexpr int V = C * sizeof(T) > 16 ? 16 / sizeof(T) : C;
+    typedef T vec __attribute__((ext_vector_type(V)));
+    typedef __attribute__((address_space(1))) vec gvec;  // (global, not flat)
+#pragma unroll
+    for (int c = 0; c < C; c += V) {
+        vec t;
+#pragma unroll
+        for (int j = 0; j < V; ++j)
+            t[j] = v[c + j];
+        *(gvec *)((char *)(row + c) + off * (unsigned)sizeof(T)) = t;
+    }
 }
 
 // Makes the values of an array opaque between two passes: otherwise the
@@ -109,8 +169,7 @@ __device__ __forceinline__ void repin(float (&v)[R])
         RD_PIN(v[i]);
 }
 
-// Value of the lane to the west / east; zero at the wave's ends, which are
-// the domain's edges.
+// Value of the lane to the west / east (zero at the wave's ends).
 __device__ __forceinline__ float from_west(float v)
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v),
@@ -124,36 +183,97 @@ __device__ __forceinline__ float from_east(float v)
 __device__ __forceinline__ double from_west(double v) { return dpp_f64<0x138, 0xF>(v); }
 __device__ __forceinline__ double from_east(double v) { return dpp_f64<0x130, 0xF>(v); }
 
-// Fragments of Q, Q^T and the eigenvalues (once per workgroup).
-template <int N>
-__device__ void init_tables(Lds<N> &s)
+// Sums of up to four values over a wave at once: exchanging halves, then
+// quarters, between pairs of values leaves row m of the wave (lanes 16 m ..)
+// with the partial sums of value {0, 2, 1, 3}[m], and four row shifts add
+// them up in the row's last lane: 21 instructions for four values, where one
+// value alone takes 18.
+__device__ __forceinline__ double swap_add32(double a, double b)
 {
-    constexpr int KS = Layout<N>::KS, T = Layout<N>::T;
-    const float nrm = sqrtf(2.0f / (float)N);
-    for (int t = threadIdx.x; t < N * N; t += T) {
-        const int e = t & 7, l = (t >> 3) & 63, f = t >> 9;
-        const int row = (f / KS) * 16 + (l & 15), col = (f % KS) * 32 + 8 * (l >> 4) + e;
-        // Q[k][i] = nrm cos(pi k (2 i + 1) / 2N), row 0 scaled by 1/sqrt(2);
-        // the angle is reduced exactly in integers
-        const float qv = cospif((float)((row * (2 * col + 1)) % (4 * N)) / (float)(2 * N)) *
-                         (row == 0 ? sqrtf(1.0f / (float)N) : nrm);
-        const float tv = cospif((float)((col * (2 * row + 1)) % (4 * N)) / (float)(2 * N)) *
-                         (col == 0 ? sqrtf(1.0f / (float)N) : nrm);
-        s.qf[t] = (_Float16)qv;
-        s.qt[t] = (_Float16)tv;
+    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto hi =
+        __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+    return __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
+           __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+}
+__device__ __forceinline__ double swap_add16(double a, double b)
+{
+    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto hi =
+        __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+    return __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
+           __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+}
+
+// Workgroup sums of M values through slot[M][W]; every wave gets them in the
+// same order of additions.
+template <int W, int M>
+__device__ __forceinline__ void group_sum(double (&v)[M], double *slot, int w)
+{
+    if constexpr (M < 3) {
+        block_sum_n<W>(v, slot, w);
+    } else {
+        const int lane = lane_here(), row = lane >> 4;
+        const int m = row == 1 ? 2 : row == 2 ? 1 : row;
+#pragma unroll
+        for (int m0 = 0; m0 < M; m0 += 4) {
+            const double a = swap_add32(v[m0], m0 + 1 < M ? v[m0 + 1] : 0.0);
+            const double b = swap_add32(m0 + 2 < M ? v[m0 + 2] : 0.0, m0 + 3 < M ? v[m0 + 3] : 0.0);
+            double t = swap_add16(a, b);
+            t += dpp_f64<0x111, 0xF>(t);  // row_shr:1, 2, 4, 8
+            t += dpp_f64<0x112, 0xF>(t);
+            t += dpp_f64<0x114, 0xF>(t);
+            t += dpp_f64<0x118, 0xF>(t);
+            if ((lane & 15) == 15 && m0 + m < M)
+                slot[(m0 + m) * W + w] = t;
+        }
+        __syncthreads();
+        slots_sum<W>(v, slot);
     }
-    for (int k = threadIdx.x; k < N; k += T)
-        s.lam[k] = 2.0f - 2.0f * cospif((float)k / (float)N);
+}
+
+// Q[k][i] = nrm cos(pi k (2 i + 1) / 2N), row 0 scaled by 1/sqrt(2); the
+// angle is reduced exactly in integers.
+template <int N>
+__device__ __forceinline__ float dct(int k, int i)
+{
+    return cospif((float)((k * (2 * i + 1)) % (4 * N)) / (float)(2 * N)) *
+           sqrtf((k == 0 ? 1.0f : 2.0f) / (float)N);
+}
+
+// Row and column of value t of a table in fragment order.
+template <class S>
+__device__ __forceinline__ void fragment_entry(int t, int &row, int &col)
+{
+    const int e = t & 7, l = (t >> 3) & 63, f = t >> 9;
+    row = (f / S::KS) * 16 + (l & 15);
+    col = (f % S::KS) * 32 + 8 * (l >> 4) + e;
+}
+
+// Fragments of Q, Q^T and the eigenvalues (once per workgroup).
+template <class S>
+__device__ void init_tables(Lds<S> &s)
+{
+    for (int t = threadIdx.x; t < S::N * S::N; t += S::T) {
+        int row, col;
+        fragment_entry<S>(t, row, col);
+        s.qf[t] = (_Float16)dct<S::N>(row, col);
+        s.qt[t] = (_Float16)dct<S::N>(col, row);
+    }
+    for (int k = threadIdx.x; k < S::N; k += S::T)
+        s.lam[k] = 2.0f - 2.0f * cospif((float)k / (float)S::N);
     __syncthreads();
 }
 
-// Row r (0 .. 15) of wave w's part of z: rows 0-7 lie in the wave's own part
-// of x, rows 8-15 in its part of y (both are free when z is formed).
-template <int N>
-__device__ __forceinline__ float *z_row(Lds<N> &s, int w, int r)
+// Row j of z: of the 16 rows of a tile the first 8 lie in the tile's own
+// part of x, the others in its part of y (both are free when z is formed).
+template <class S>
+__device__ __forceinline__ float *z_row(Lds<S> &s, int j)
 {
-    _Float16 *base = (r < 8 ? s.x : s.y) + w * kRows * Layout<N>::SN;
-    return (float *)base + (r & 7) * Layout<N>::ZN;
+    _Float16 *base = (j & 8 ? s.y : s.x) + (j >> 4) * 16 * S::SN;
+    return (float *)base + (j & 7) * S::ZN;
 }
 
 __device__ __forceinline__ f32x4 mfma(half8 a, half8 b, f32x4 c)
@@ -161,14 +281,19 @@ __device__ __forceinline__ f32x4 mfma(half8 a, half8 b, f32x4 c)
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
 
-// One transform stage of a wave: for each of the N / 16 tiles of the table m
-// the 16 x 16 product with the wave's own 16 rows a (kTableFirst: the table
-// gives the result's rows, otherwise its columns), handed to f(tile, acc).
-// The next tile's fragments are read during the present one's products.
-template <int N, bool kTableFirst, typename F>
-__device__ __forceinline__ void product(const _Float16 *m, const half8 (&a)[Layout<N>::KS], F &&f)
+__device__ __forceinline__ half4 to_half(f32x4 v)
 {
-    constexpr int KS = Layout<N>::KS, NT = Layout<N>::W;
+    return half4{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
+}
+
+// One transform stage of a wave: for each of the table's tiles the 16 x 16
+// product with the wave's 16 rows a (kTableFirst: the table gives the
+// result's rows, otherwise its columns), handed to f(tile, acc).  The next
+// tile's fragments are read during the present one's products.
+template <class S, bool kTableFirst, typename F>
+__device__ __forceinline__ void product(const _Float16 *m, const half8 (&a)[S::KS], F &&f)
+{
+    constexpr int KS = S::KS, NT = S::NT;
     const _Float16 *ml = m + lane_here() * 8;
     half8 b[2][KS];
 #pragma unroll
@@ -190,6 +315,87 @@ __device__ __forceinline__ void product(const _Float16 *m, const half8 (&a)[Layo
     }
 }
 
+// What a thread knows of its place and its item's arrays.
+template <class S>
+struct Ctx {
+    Lds<S> &s;
+    double *xs;       // fields (slot)
+    float *hs;        // increments [species][buffer]
+    int w;            // wave
+    unsigned o;       // this lane's offset from row(k) of its wave
+    unsigned os, on;  // offsets of the rows below and above the strip
+
+    __device__ Ctx(Lds<S> &lds, void *slot, int n_fields) : s(lds)
+    {
+        xs = (double *)slot;
+        hs = (float *)(xs + (size_t)n_fields * S::cells);
+        w = wave_index();
+        const int st = strip(), col = lane() * S::C;
+        o = S::LW == 64 ? col : (st % (64 / S::LW)) * S::K * S::N + col;
+        // mirror rows at the domain's edges: the strip's own edge row
+        os = (st > 0 ? st * S::K - 1 : 0) * S::N + col;
+        on = (st < S::ST - 1 ? (st + 1) * S::K : S::M - 1) * S::N + col;
+    }
+    // Offset of row k of this wave('s first strip) in an array.
+    __device__ int row(int k) const { return (w * (64 / S::LW) * S::K + k) * S::N; }
+    __device__ int strip() const { return S::LW == 64 ? w : (int)threadIdx.x / S::LW; }
+    __device__ int lane() const { return (int)threadIdx.x % S::LW; }
+    __device__ double *field(int k) const { return opaque(xs + (size_t)k * S::cells); }
+    __device__ float *h(int sp, int k) const { return opaque(hs + (size_t)(2 * sp + k) * S::cells); }
+    __device__ size_t cell0() const { return 0; }  // first cell of the workgroup's rows
+
+    // Sums over the item's threads; also a barrier of the item.
+    template <int M>
+    __device__ void sum(double (&v)[M], int slot)
+    {
+        group_sum<S::W>(v, s.red + slot, w);
+    }
+    __device__ double sum1(double v, int slot)
+    {
+        double t[1] = {v};
+        sum(t, slot);
+        return t[0];
+    }
+    __device__ void sync() { __syncthreads(); }
+    __device__ bool failed() const { return false; }
+    __device__ bool leader() const { return threadIdx.x == 0; }
+    // Rows below and above the strip of a field, an increment, and z.
+    __device__ void halo(int k, double (&lo)[S::C], double (&hi)[S::C]) const
+    {
+        load_cols(field(k), opaque(os), lo);
+        load_cols(field(k), opaque(on), hi);
+    }
+    __device__ void halo(int sp, int k, float (&lo)[S::C], float (&hi)[S::C]) const
+    {
+        load_cols(h(sp, k), opaque(os), lo);
+        load_cols(h(sp, k), opaque(on), hi);
+    }
+    __device__ void halo_z(float (&lo)[S::C], float (&hi)[S::C]) const
+    {
+        const int st = strip(), l = lane() * S::C;
+        const float *a = z_row<S>(s, st > 0 ? st * S::K - 1 : 0) + l;
+        const float *b = z_row<S>(s, st < S::ST - 1 ? (st + 1) * S::K : S::N - 1) + l;
+#pragma unroll
+        for (int c = 0; c < S::C; ++c) {
+            lo[c] = a[c];
+            hi[c] = b[c];
+        }
+    }
+    // z = r (no preconditioner)
+    __device__ void set_z(const float (&r)[S::R]) const
+    {
+#pragma unroll
+        for (int k = 0; k < S::K; ++k)
+#pragma unroll
+            for (int c = 0; c < S::C; ++c)
+                z_row<S>(s, strip() * S::K + k)[lane() * S::C + c] = r[k * S::C + c];
+    }
+    // A group of workgroups also hands its edge rows to its neighbours.
+    __device__ void put_edge(int, int, const double (&)[S::C]) const {}
+    __device__ void put_edge(int, int, int, const float (&)[S::C]) const {}
+    __device__ void put_edge_z(const float (&)[S::R]) const {}
+};
+
 // z = M^-1 r (own cells; the rows also stay in LDS for the neighbours after
 // the caller's next barrier).  scale: power of two that brings r near 1;
 // cs = c / sbar; out = 1 / (scale sbar).
@@ -201,71 +407,71 @@ __device__ __forceinline__ void product(const _Float16 *m, const half8 (&a)[Layo
 // of its slice for either operand; the result holds column l % 16, rows
 // 4 (l / 16) .. + 3, and the operands are placed so that those four values
 // are neighbours in the next stage's rows.
-template <int N>
-__device__ __forceinline__ void apply_precond(Lds<N> &s, const float (&r)[Layout<N>::R],
-                                              float (&z)[Layout<N>::R], float scale, float cs,
-                                              float out, int w)
+template <class S>
+__device__ __forceinline__ void apply_precond(const Ctx<S> &x, const float (&r)[S::R],
+                                              float (&z)[S::R], float scale, float cs, float out)
 {
-    using L = Layout<N>;
-    constexpr int C = L::C, KS = L::KS, SN = L::SN;
+    constexpr int C = S::C, KS = S::KS, SN = S::SN;
+    static_assert(S::NT == S::W, "one row tile per wave");
+    Lds<S> &s = x.s;
     const int lane = lane_here(), lr = lane & 15, lq = lane >> 4;
-    _Float16 *xo = s.x + w * kRows * SN;  // own 16 rows
-    _Float16 *yo = s.y + w * kRows * SN;
+    const int st = x.strip();
+    {
+        _Float16 *xo = s.x + st * S::K * SN + x.lane() * C;
 #pragma unroll
-    for (int k = 0; k < kRows; ++k) {
+        for (int k = 0; k < S::K; ++k) {
 #pragma unroll
-        for (int c = 0; c < C; ++c)
-            xo[k * SN + lane * C + c] = (_Float16)(r[k * C + c] * scale);
-        if (k % 4 == 3)
-            group_end();
+            for (int c = 0; c < C; ++c)
+                xo[k * SN + c] = (_Float16)(r[k * C + c] * scale);
+            if (k % 4 == 3)
+                group_end();
+        }
     }
     wave_sync();
     half8 a[KS];
-    auto rows = [&](const _Float16 *x) {  // the fragments of 16 rows
+    auto rows = [&](const _Float16 *p) {  // the fragments of 16 rows
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
-            a[ks] = *(const half8 *)&x[lr * SN + ks * 32 + lq * 8];
+            a[ks] = *(const half8 *)&p[lr * SN + ks * 32 + lq * 8];
     };
+    const int t0 = x.w * 16;
     // stage 1: T[j][k] = sum_i r[j][i] Q[k][i], own rows j -> y[k][j]
-    rows(xo);
-    product<N, false>(s.qf, a, [&](int nt, f32x4 acc) {
-        const half4 h = {(_Float16)acc[0], (_Float16)acc[1], (_Float16)acc[2], (_Float16)acc[3]};
-        *(half4 *)&s.y[(nt * 16 + lr) * SN + w * kRows + lq * 4] = h;
+    rows(s.x + t0 * SN);
+    product<S, false>(s.qf, a, [&](int nt, f32x4 acc) {
+        *(half4 *)&s.y[(nt * 16 + lr) * SN + t0 + lq * 4] = to_half(acc);
     });
     __syncthreads();
     // stage 2: U[q][k] = sum_j Q[q][j] T[j][k], own modes k, divided by
     // 1 + cs (lam_q + lam_k) -> y[k][q] in place
-    rows(yo);
+    rows(s.y + t0 * SN);
     wave_sync();
-    const float base = fmaf(cs, s.lam[w * kRows + lr], 1.0f);
-    product<N, true>(s.qf, a, [&](int nt, f32x4 acc) {
+    const float base = fmaf(cs, s.lam[t0 + lr], 1.0f);
+    product<S, true>(s.qf, a, [&](int nt, f32x4 acc) {
         const f32x4 lam = *(const f32x4 *)&s.lam[nt * 16 + lq * 4];
-        half4 h;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            h[i] = (_Float16)(acc[i] * __builtin_amdgcn_rcpf(fmaf(cs, lam[i], base)));
-        *(half4 *)&yo[lr * SN + nt * 16 + lq * 4] = h;
+            acc[i] *= __builtin_amdgcn_rcpf(fmaf(cs, lam[i], base));
+        *(half4 *)&s.y[(t0 + lr) * SN + nt * 16 + lq * 4] = to_half(acc);
     });
     wave_sync();
     // stage 3: V[j][k] = sum_q Q[q][j] U[q][k], own modes k -> x[j][k]
-    rows(yo);
-    product<N, false>(s.qt, a, [&](int nt, f32x4 acc) {
-        const half4 h = {(_Float16)acc[0], (_Float16)acc[1], (_Float16)acc[2], (_Float16)acc[3]};
-        *(half4 *)&s.x[(nt * 16 + lr) * SN + w * kRows + lq * 4] = h;
+    rows(s.y + t0 * SN);
+    product<S, false>(s.qt, a, [&](int nt, f32x4 acc) {
+        *(half4 *)&s.x[(nt * 16 + lr) * SN + t0 + lq * 4] = to_half(acc);
     });
     __syncthreads();
     // stage 4: z[j][i] = sum_k V[j][k] Q[k][i], own rows j
-    rows(xo);
+    rows(s.x + t0 * SN);
     wave_sync();
-    float *zr = z_row<N>(s, w, lr);
-    product<N, true>(s.qt, a, [&](int nt, f32x4 acc) {
+    float *zr = z_row<S>(s, t0 + lr);
+    product<S, true>(s.qt, a, [&](int nt, f32x4 acc) {
         acc *= out;
         *(f32x4 *)&zr[nt * 16 + lq * 4] = acc;
     });
     wave_sync();
 #pragma unroll
-    for (int k = 0; k < kRows; ++k) {
-        const float *p = z_row<N>(s, w, k) + lane * C;
+    for (int k = 0; k < S::K; ++k) {
+        const float *p = z_row<S>(s, st * S::K + k) + x.lane() * C;
 #pragma unroll
         for (int c = 0; c < C; ++c)
             z[k * C + c] = p[c];
@@ -277,20 +483,19 @@ __device__ __forceinline__ void apply_precond(Lds<N> &s, const float (&r)[Layout
 // differences are formed, not the neighbours' sum: for a smooth p the sum's
 // rounding, scaled by 4 c, is the same in many cells at once and would act on
 // the smooth part of the increment (measured: relative error 1.3e-6 instead
-// of 4e-8 after 100 steps of 128 x 128 prior draws).
-template <int N, typename F>
-__device__ __forceinline__ void stencil(const float (&p)[Layout<N>::R],
-                                        const float (&hs)[Layout<N>::C],
-                                        const float (&hn)[Layout<N>::C], F &&f)
+// of 2.5e-8 after 100 steps of 128 x 128 prior draws).
+template <class S, typename F>
+__device__ __forceinline__ void stencil(const float (&p)[S::R], const float (&hs)[S::C],
+                                        const float (&hn)[S::C], F &&f)
 {
-    constexpr int C = Layout<N>::C;
-    const bool east_edge = lane_here() == 63;
+    constexpr int C = S::C, K = S::K;
+    const bool east_edge = (lane_here() & (S::LW - 1)) == S::LW - 1;
     float ds[C];
 #pragma unroll
     for (int c = 0; c < C; ++c)
         ds[c] = p[c] - hs[c];
 #pragma unroll
-    for (int k = 0; k < kRows; ++k) {
+    for (int k = 0; k < K; ++k) {
         float de[C];  // east neighbour - own, zero across the domain's edge
 #pragma unroll
         for (int c = 0; c < C - 1; ++c)
@@ -301,11 +506,11 @@ __device__ __forceinline__ void stencil(const float (&p)[Layout<N>::R],
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const float own = p[k * C + c];
-            const float dn = (k < kRows - 1 ? p[(k + 1) * C + c] : hn[c]) - own;
+            const float dn = (k < K - 1 ? p[(k + 1) * C + c] : hn[c]) - own;
             f(k * C + c, own, ((c > 0 ? de[c - 1] : dw) - de[c]) + (ds[c] - dn));
             ds[c] = dn;
         }
-        if ((k * C) % 4 == 4 - C)
+        if ((k * C) % 4 == 4 - C || C == 4)
             group_end();
     }
 }
@@ -315,83 +520,73 @@ struct System {
     double inv_dt, c, src, e0, g;  // e = e0 - g u v (u) or e0 + g u^2 (v)
 };
 
-template <int N>
-struct Ctx {
-    using L = Layout<N>;
-    Lds<N> &s;
-    double *xs;          // X_u, X_v (slot)
-    float *hs;           // increments [species][buffer]
-    int w, o, os, on;    // wave, own / south / north row offsets of this lane
-
-    __device__ double *field(int sp) const { return xs + (size_t)sp * (N * N); }
-    __device__ float *h(int sp, int k) const { return hs + (size_t)(2 * sp + k) * (N * N); }
-
-    __device__ Ctx(Lds<N> &lds, void *slot) : s(lds)
-    {
-        xs = (double *)slot;
-        hs = (float *)(xs + 2 * N * N);
-        w = wave_index();
-        const int lane = threadIdx.x & 63;
-        o = (w * kRows) * N + lane * L::C;
-        // mirror rows at the domain's edges: the strip's own edge row
-        os = w > 0 ? o - N : o;
-        on = w < L::W - 1 ? o + kRows * N : o + (kRows - 1) * N;
-    }
-};
-
 // Residual of the level-n field, r = src - e x - c t(x) in FP64 rounded once,
-// sg = sigma = 1/dt + e, and this thread's sums of b^2, r^2 and e.  kSp = 1
-// also advances u by its increment du (whose system is solved by then; the v
-// system uses u of level n, which is read here for the last time) and
-// records du in h_u.
-template <int N, int kSp>
-__device__ __forceinline__ void residual(const Ctx<N> &x, const System &y,
-                                         float (&r)[Layout<N>::R], float (&sg)[Layout<N>::R],
-                                         double &bb, double &rr, double &es,
-                                         const float (&du)[Layout<N>::R], float *h_u)
+// sg = sigma = 1/dt + e, and this thread's sums of b^2, r^2 and e.
+// fo, ft: field buffers of this species and of the other one.
+// kAdvance: the other species is one increment d behind (its system of the
+// step that it belongs to is solved; u of level n is read here for the last
+// time in the v system, v is first read at its new level in the next u
+// system): it is advanced on the way, and d recorded in increment buffer hb.
+template <class S, int kSp, bool kAdvance>
+__device__ __forceinline__ void residual(const Ctx<S> &x, const System &y, int fo, int ft,
+                                         float (&r)[S::R], float (&sg)[S::R], double &bb,
+                                         double &rr, double &es, const float (&d)[S::R], int hb)
 {
-    using L = Layout<N>;
-    constexpr int C = L::C;
-    const double *own = x.field(kSp), *oth = x.field(1 - kSp);
-    double *adv = x.field(0);
-    const int lane = lane_here(), o = opaque(x.o);
+    constexpr int C = S::C, N = S::N, K = S::K, R = S::R;
+    const double *own = x.field(fo) + x.row(0);
+    double *oth = x.field(ft) + x.row(0);
+    float *hd = x.h(1 - kSp, hb) + x.row(0);
+    const int lane = lane_here() & (S::LW - 1);
+    const unsigned o = opaque(x.o);
     double cnt[C];
 #pragma unroll
     for (int c = 0; c < C; ++c)
-        cnt[c] = 4.0 - (c == 0 && lane == 0 ? 1.0 : 0.0) - (c == C - 1 && lane == 63 ? 1.0 : 0.0);
+        cnt[c] = 4.0 - (c == 0 && lane == 0 ? 1.0 : 0.0) -
+                 (c == C - 1 && lane == S::LW - 1 ? 1.0 : 0.0);
     // kG rows of both fields are loaded while the kG rows before them are
     // worked on
-    constexpr int kG = 4;
-    double cur[C], so[C], nx[2][kG][C], ot[2][kG][C];
+    constexpr int kG = K <= 4 || R <= 16 || C >= 4 ? 2 : 4;
+    double cur[C], so[C], last[C], nx[2][kG][C], ot[2][kG][C];
     auto load = [&](int k0, double (&nn)[kG][C], double (&oo)[kG][C]) {
 #pragma unroll
-        for (int j = 0; j < kG; ++j)
+        for (int j = 0; j < kG; ++j) {
+            const int k = k0 + j;
+            if (k < K - 1) {
+                load_cols(own + (k + 1) * N, o, nn[j]);
+            } else {
 #pragma unroll
-            for (int c = 0; c < C; ++c) {
-                const int k = k0 + j;
-                nn[j][c] = k < kRows - 1 ? own[o + (k + 1) * N + c] : own[x.on + c];
-                oo[j][c] = oth[o + k * N + c];
+                for (int c = 0; c < C; ++c)
+                    nn[j][c] = last[c];
             }
+            load_cols(oth + k * N, o, oo[j]);
+        }
     };
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-        cur[c] = own[o + c];
-        so[c] = own[x.os + c];
-    }
+    x.halo(fo, so, last);
+    load_cols(own, o, cur);
     load(0, nx[0], ot[0]);
     bb = rr = es = 0.0;
 #pragma unroll
-    for (int k0 = 0; k0 < kRows; k0 += kG) {
+    for (int k0 = 0; k0 < K; k0 += kG) {
         const int ph = (k0 / kG) & 1;
-        if (k0 + kG < kRows)
+        if (k0 + kG < K)
             load(k0 + kG, nx[ph ^ 1], ot[ph ^ 1]);
 #pragma unroll
         for (int j = 0; j < kG; ++j) {
             const int k = k0 + j;
-            const double ww = from_west(cur[C - 1]), ee = from_east(cur[0]);
+            double ww = from_west(cur[C - 1]), ee = from_east(cur[0]);
+            if constexpr (S::LW < 64) {  // the strips of a wave are not neighbours here
+                ww = lane == 0 ? 0.0 : ww;
+                ee = lane == S::LW - 1 ? 0.0 : ee;
+            }
+            double xn[C];
+            float dk[C];
 #pragma unroll
             for (int c = 0; c < C; ++c) {
-                const double xc = cur[c], sc = ot[ph][j][c];
+                const int i = k * C + c;
+                double xc = cur[c], sc = ot[ph][j][c];
+                dk[c] = d[i];
+                if constexpr (kAdvance && kSp == 0)  // v is read at its new level
+                    sc += (double)dk[c];
                 const double wv = c > 0 ? cur[c - 1] : ww;
                 const double ev = c < C - 1 ? cur[c + 1] : ee;
                 const double t = fma(cnt[c], xc, -((wv + ev) + (so[c] + nx[ph][j][c])));
@@ -400,20 +595,26 @@ __device__ __forceinline__ void residual(const Ctx<N> &x, const System &y,
                 const double b = fma(xc, y.inv_dt, y.src);
                 bb = fma(b, b, bb);
                 rr = fma(res, res, rr);
-                es += e;
+                if (c == 0)  // (any good mean of sigma will do)
+                    es += e;
                 float rf = (float)res, sf = (float)(y.inv_dt + e);
                 RD_PIN(rf);
                 RD_PIN(sf);
                 RD_PIN(bb);
                 RD_PIN(rr);
                 RD_PIN(es);
-                if constexpr (kSp == 1) {
-                    const float dk = du[k * C + c];
-                    adv[o + k * N + c] = sc + (double)dk;
-                    h_u[o + k * N + c] = dk;
+                if constexpr (kAdvance)
+                    xn[c] = kSp == 0 ? sc : sc + (double)dk[c];
+                r[i] = rf;
+                sg[i] = sf;
+            }
+            if constexpr (kAdvance) {
+                store_cols(oth + k * N, o, xn);
+                store_cols(hd + k * N, o, dk);
+                if (k == 0 || k == K - 1) {
+                    x.put_edge(ft, k, xn);
+                    x.put_edge(1 - kSp, hb, k, dk);
                 }
-                r[k * C + c] = rf;
-                sg[k * C + c] = sf;
             }
 #pragma unroll
             for (int c = 0; c < C; ++c) {
@@ -426,84 +627,87 @@ __device__ __forceinline__ void residual(const Ctx<N> &x, const System &y,
     }
 }
 
-// Preconditioned CG for the increment d of one species; r, sg from
-// residual().  h1, h2: the increments of the last two steps; npred is the
-// number of them that the start vector d0 = w1 h1 + w2 h2 uses, with the
-// Galerkin weights (h_i, r0 - A d0) = 0 (the start of least energy-norm
-// error over their span).  The stopping test is |r| <= rtol |b| on the
-// recursively updated residual.
-template <int N>
-__device__ int solve(const Ctx<N> &x, const System &y, float (&r)[Layout<N>::R],
-                     const float (&sg)[Layout<N>::R], float (&d)[Layout<N>::R], double bb,
-                     double rr, double es, const float *h1, const float *h2, int npred,
-                     double rtol2, int maxit, int &it_acc, int &quiet)
+// Own cells of a slot array.
+template <class S>
+__device__ __forceinline__ void load_strip(const Ctx<S> &x, const float *a, float (&v)[S::R])
 {
-    using L = Layout<N>;
-    using RS = RedSlots<L::W>;
-    constexpr int C = L::C, R = L::R, W = L::W;
-    double *red = x.s.red;
+    const float *row = a + x.row(0);
+    const unsigned o = opaque(x.o);
+#pragma unroll
+    for (int k = 0; k < S::K; ++k) {
+        float t[S::C];
+        load_cols(row + k * S::N, o, t);
+#pragma unroll
+        for (int c = 0; c < S::C; ++c)
+            v[k * S::C + c] = t[c];
+    }
+}
+
+// The scalars of one solve that its passes share.
+struct Scalars {
+    double bb, rr, sbar, rtol2;
+    int maxit, it;
+};
+
+// Start vector d0 = w1 h1 + w2 h2 from the increments of the last two steps
+// (npred of them), with the Galerkin weights (h_i, r0 - A d0) = 0: the start
+// of least energy-norm error over their span.  r becomes the residual of d0.
+// On entry bb, rr hold this thread's sums and es its sum of e; on return v
+// holds the item's.  `quiet`: r0 itself met the tolerance.
+template <class S>
+__device__ __forceinline__ void start(Ctx<S> &x, const System &y, int sp, int kn, int npred,
+                                      float (&r)[S::R], const float (&sg)[S::R], float (&d)[S::R],
+                                      double es, Scalars &v, int &quiet)
+{
+    using RS = RedSlots<S::W>;
+    constexpr int C = S::C, R = S::R, K = S::K, N = S::N;
     const float cf = uniform((float)y.c);
-    float p[R], q[R];
     if (npred > 0) {
-        float s1[C], n1[C], s2[C], n2[C];
+        float p[R], s1[C], n1[C], s2[C], n2[C];
         double g11 = 0.0, g12 = 0.0, g22 = 0.0, b1 = 0.0, b2 = 0.0;
-        const int o = opaque(x.o);
+        load_strip(x, x.h(sp, kn ^ 1), p);
 #pragma unroll
-        for (int k = 0; k < kRows; ++k)
+        for (int i = 0; i < R; ++i)
+            d[i] = 0.0f;
+        x.halo(sp, kn ^ 1, s1, n1);
 #pragma unroll
-            for (int c = 0; c < C; ++c) {
-                p[k * C + c] = h1[o + k * N + c];
-                d[k * C + c] = 0.0f;
-            }
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            s1[c] = h1[x.os + c];
-            n1[c] = h1[x.on + c];
+        for (int c = 0; c < C; ++c)
             s2[c] = n2[c] = 0.0f;
-        }
         if (npred > 1) {
-#pragma unroll
-            for (int k = 0; k < kRows; ++k)
-#pragma unroll
-                for (int c = 0; c < C; ++c)
-                    d[k * C + c] = h2[o + k * N + c];
-#pragma unroll
-            for (int c = 0; c < C; ++c) {
-                s2[c] = h2[x.os + c];
-                n2[c] = h2[x.on + c];
-            }
+            load_strip(x, x.h(sp, kn), d);
+            x.halo(sp, kn, s2, n2);
         }
-        stencil<N>(p, s1, n1, [&](int i, float own, float t5) {
+        stencil<S>(p, s1, n1, [&](int i, float own, float t5) {
             float w = fmaf(cf, t5, sg[i] * own);  // (A h1) at the cell
             RD_PIN(w);
             g11 = fma((double)own, (double)w, g11);
             g12 = fma((double)d[i], (double)w, g12);
             b1 = fma((double)own, (double)r[i], b1);
+            b2 = fma((double)d[i], (double)r[i], b2);
             RD_PIN(g11);
             RD_PIN(g12);
             RD_PIN(b1);
+            RD_PIN(b2);
         });
         repin(d);
         repin(r);
-        stencil<N>(d, s2, n2, [&](int i, float own, float t5) {
+        stencil<S>(d, s2, n2, [&](int i, float own, float t5) {
             float w = fmaf(cf, t5, sg[i] * own);  // (A h2) at the cell
             RD_PIN(w);
             g22 = fma((double)own, (double)w, g22);
-            b2 = fma((double)own, (double)r[i], b2);
             RD_PIN(g22);
-            RD_PIN(b2);
         });
-        double v8[8] = {bb, rr, es, g11, g12, g22, b1, b2};
-        block_sum_n<W>(v8, red + RS::gram, x.w);
-        bb = v8[0];
-        rr = v8[1];
+        double v8[8] = {v.bb, v.rr, es, g11, g12, g22, b1, b2};
+        x.sum(v8, RS::gram);
+        v.bb = v8[0];
+        v.rr = v8[1];
         es = v8[2];
         g11 = v8[3];
         g12 = v8[4];
         g22 = v8[5];
         b1 = v8[6];
         b2 = v8[7];
-        quiet = uniform((int)!(rr > rtol2 * bb));
+        quiet = uniform((int)!(v.rr > v.rtol2 * v.bb));
         double w1 = 0.0, w2 = 0.0;
         const double det = g11 * g22 - g12 * g12;
         if (g11 > 0.0 && g22 > 0.0 && finite(det) && det > 1e-12 * g11 * g22 && finite(b1) &&
@@ -514,7 +718,7 @@ __device__ int solve(const Ctx<N> &x, const System &y, float (&r)[Layout<N>::R],
             w1 = b1 / g11;  // one increment only, or a (nearly) dependent pair
         }
         const float W1 = uniform((float)w1), W2 = uniform((float)w2);
-        if (finite(rr)) {
+        if (finite(v.rr)) {
             repin(p);
             repin(r);
             repin(d);
@@ -529,68 +733,94 @@ __device__ int solve(const Ctx<N> &x, const System &y, float (&r)[Layout<N>::R],
                 n1[c] = fmaf(W1, n1[c], W2 * n2[c]);
             }
             double t = 0.0;
-            stencil<N>(d, s1, n1, [&](int i, float own, float t5) {
-                float v = r[i] - fmaf(cf, t5, sg[i] * own);
-                RD_PIN(v);
-                r[i] = v;
-                t = fma((double)v, (double)v, t);
+            stencil<S>(d, s1, n1, [&](int i, float own, float t5) {
+                float w = r[i] - fmaf(cf, t5, sg[i] * own);
+                RD_PIN(w);
+                r[i] = w;
+                t = fma((double)w, (double)w, t);
                 RD_PIN(t);
             });
             repin(r);
-            rr = block_sum<W>(t, red + RS::rr, x.w);
+            v.rr = x.sum1(t, RS::rr);
         }
     } else {
-        double v3[3] = {bb, rr, es};
-        block_sum_n<W>(v3, red + RS::gram, x.w);
-        bb = v3[0];
-        rr = v3[1];
+        double v3[3] = {v.bb, v.rr, es};
+        x.sum(v3, RS::gram);
+        v.bb = v3[0];
+        v.rr = v3[1];
         es = v3[2];
-        quiet = uniform((int)!(rr > rtol2 * bb));
+        quiet = uniform((int)!(v.rr > v.rtol2 * v.bb));
 #pragma unroll
         for (int i = 0; i < R; ++i)
             d[i] = 0.0f;
     }
-    const double tol2 = rtol2 * bb;
-    int st = (finite(bb) && finite(rr)) ? 0 : kStNonfinite;
-    int it = 0;
     // mean of sigma; the preconditioner stays positive definite whatever the
     // reaction term does
-    double sbar = y.inv_dt + es * (1.0 / ((double)N * N));
-    if (!(sbar > 0.25 * y.inv_dt) || !finite(sbar))
-        sbar = y.inv_dt;
-    const float cs = uniform((float)(y.c / sbar));
+    v.sbar = y.inv_dt + es * (1.0 / ((double)N * S::LW));
+    if (!(v.sbar > 0.25 * y.inv_dt) || !finite(v.sbar))
+        v.sbar = y.inv_dt;
+}
+
+// A cap on the iterations below this asks for a bound on plain CG's work (a
+// preconditioned iteration does the work of several): the iteration then runs
+// without the preconditioner, and solves that such a cap stops are stopped
+// as before.
+constexpr int kPlainCap = 16;
+
+// Preconditioned CG: d += A^-1 r until |r|^2 <= stop2 (r is updated
+// recursively).  Returns RD status bits.
+template <class S>
+__device__ __forceinline__ int pcg(Ctx<S> &x, const System &y, float (&r)[S::R],
+                                   const float (&sg)[S::R], float (&d)[S::R], double stop2,
+                                   Scalars &v)
+{
+    using RS = RedSlots<S::W>;
+    constexpr int C = S::C, R = S::R, N = S::N;
+    const float cf = uniform((float)y.c);
+    const float cs = uniform((float)(y.c / v.sbar));
+    float p[R], q[R], ps[C], pn[C];
     double rz_old = 1.0;
-    float ps[C], pn[C];
-    while (st == 0 && rr > tol2) {
-        if (it >= maxit) {
+    int st = (finite(v.bb) && finite(v.rr)) ? 0 : kStNonfinite;
+    bool first = true;
+    while (st == 0 && v.rr > stop2) {
+        if (x.failed()) {
+            st = kStGroupTimeout;
+            break;
+        }
+        if (v.it >= v.maxit) {
             st = kStNotConverged;
             break;
         }
         // power of two near the r.m.s. residual (the FP16 stages see values
         // near 1; one coefficient can hold all of |r|, at most N)
-        int ex = uniform(__builtin_amdgcn_frexp_exp(rr * (1.0 / ((double)N * N)))) >> 1;
+        int ex = uniform(__builtin_amdgcn_frexp_exp(v.rr * (1.0 / ((double)N * N)))) >> 1;
         ex = ex < -100 ? -100 : ex > 100 ? 100 : ex;
         const float scale = ldexpf(1.0f, -ex);
-        const float out = uniform((float)(ldexp(1.0, ex) / sbar));
-        apply_precond<N>(x.s, r, q, scale, cs, out, x.w);  // z in q
+        const float out = uniform((float)(ldexp(1.0, ex) / v.sbar));
+        if (v.maxit >= kPlainCap) {
+            apply_precond(x, r, q, scale, cs, out);  // z in q
+        } else {
+            x.set_z(r);
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+                q[i] = r[i];
+        }
+        x.put_edge_z(q);
         double t = 0.0;
 #pragma unroll
         for (int i = 0; i < R; ++i)
             t = fma((double)r[i], (double)q[i], t);
         repin(r);
         repin(q);
-        const double rz = block_sum<W>(t, red + RS::rz, x.w);  // (z is visible now)
+        const double rz = x.sum1(t, RS::rz);  // (z is visible now)
         if (!finite(rz)) {
             st = kStNonfinite;
             break;
         }
         // the neighbours' edge rows of p are formed here from their z
-        const float *zs = (x.w > 0 ? z_row<N>(x.s, x.w - 1, kRows - 1) : z_row<N>(x.s, 0, 0)) +
-                          (threadIdx.x & 63) * C;
-        const float *zn = (x.w < W - 1 ? z_row<N>(x.s, x.w + 1, 0)
-                                       : z_row<N>(x.s, W - 1, kRows - 1)) +
-                          (threadIdx.x & 63) * C;
-        if (it == 0) {
+        float zs[C], zn[C];
+        x.halo_z(zs, zn);
+        if (first) {
 #pragma unroll
             for (int i = 0; i < R; ++i)
                 p[i] = q[i];
@@ -610,9 +840,10 @@ __device__ int solve(const Ctx<N> &x, const System &y, float (&r)[Layout<N>::R],
                 pn[c] = fmaf(bt, pn[c], zn[c]);
             }
         }
+        first = false;
         rz_old = rz;
         t = 0.0;
-        stencil<N>(p, ps, pn, [&](int i, float own, float t5) {
+        stencil<S>(p, ps, pn, [&](int i, float own, float t5) {
             float w = fmaf(cf, t5, sg[i] * own);
             RD_PIN(w);
             q[i] = w;
@@ -621,7 +852,7 @@ __device__ int solve(const Ctx<N> &x, const System &y, float (&r)[Layout<N>::R],
         });
         repin(p);
         repin(q);
-        const double pq = block_sum<W>(t, red + RS::pq, x.w);
+        const double pq = x.sum1(t, RS::pq);
         if (!finite(pq)) {
             st = kStNonfinite;
             break;
@@ -635,49 +866,199 @@ __device__ int solve(const Ctx<N> &x, const System &y, float (&r)[Layout<N>::R],
 #pragma unroll
         for (int i = 0; i < R; ++i) {
             d[i] = fmaf(a, p[i], d[i]);
-            const float v = fmaf(-a, q[i], r[i]);
-            r[i] = v;
-            t = fma((double)v, (double)v, t);
+            const float w = fmaf(-a, q[i], r[i]);
+            r[i] = w;
+            t = fma((double)w, (double)w, t);
         }
         repin(r);
-        rr = block_sum<W>(t, red + RS::rr, x.w);
-        ++it;
-        if (!finite(rr)) {
+        v.rr = x.sum1(t, RS::rr);
+        ++v.it;
+        if (!finite(v.rr))
             st = kStNonfinite;
-            break;
-        }
     }
-    it_acc += it;
     return st;
 }
 
-// One item: all IMEX steps, then the outputs and the misfit.
-template <int N>
-__device__ void solve_item(const SolveArgs &a, int c, const GridDev &gd, Lds<N> &s, void *slot)
+// FP64 problems.  Adds the correction d to the new field fn (kFirst: to the
+// level-n field fo) and to the increment in buffer hb.
+template <class S>
+__device__ __forceinline__ void correct(const Ctx<S> &x, int sp, int fo, int fn, bool first,
+                                        const float (&d)[S::R], int hb)
 {
-    using L = Layout<N>;
-    constexpr int C = L::C, R = L::R, W = L::W, NN = N * N;
-    const Ctx<N> x(s, slot);
+    constexpr int C = S::C, N = S::N;
+    const double *from = x.field(first ? fo : fn) + x.row(0);
+    double *to = x.field(fn) + x.row(0);
+    float *hd = x.h(sp, hb) + x.row(0);
+    const unsigned o = opaque(x.o);
+#pragma unroll
+    for (int k = 0; k < S::K; ++k) {
+        double yn[C];
+        float hn[C];
+        load_cols(from + k * N, o, yn);
+        if (first) {
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                hn[c] = 0.0f;
+        } else {
+            load_cols(hd + k * N, o, hn);
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            yn[c] += (double)d[k * C + c];
+            hn[c] += d[k * C + c];
+        }
+        store_cols(to + k * N, o, yn);
+        store_cols(hd + k * N, o, hn);
+        if (k == 0 || k == S::K - 1) {
+            x.put_edge(fn, k, yn);
+            x.put_edge(sp, hb, k, hn);
+        }
+        if (k % 4 == 3)
+            group_end();
+    }
+}
+
+// FP64 problems: residual of the implicit system for the new field,
+// r = src + (x - x') / dt - e x' - c t(x'), e from the level-n fields, and
+// this thread's sum of r^2.
+template <class S>
+__device__ __forceinline__ double true_residual(const Ctx<S> &x, const System &y, int sp, int fo,
+                                                int ft, int fn, float (&r)[S::R])
+{
+    constexpr int C = S::C, N = S::N, K = S::K;
+    const double *nw = x.field(fn) + x.row(0), *own = x.field(fo) + x.row(0),
+                 *oth = x.field(ft) + x.row(0);
+    const int lane = lane_here() & (S::LW - 1);
+    const unsigned o = opaque(x.o);
+    double cur[C], so[C], last[C], rr = 0.0;
+    x.halo(fn, so, last);
+    load_cols(nw, o, cur);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        double no[C], xos[C], scs[C];
+        load_cols(own + k * N, o, xos);
+        load_cols(oth + k * N, o, scs);
+        if (k < K - 1) {
+            load_cols(nw + (k + 1) * N, o, no);
+        } else {
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                no[c] = last[c];
+        }
+        const double ww = from_west(cur[C - 1]), ee = from_east(cur[0]);
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const double xo = xos[c], sc = scs[c], xc = cur[c];
+            const double dw = c > 0 ? xc - cur[c - 1] : lane == 0 ? 0.0 : xc - ww;
+            const double de = c < C - 1 ? xc - cur[c + 1] : lane == S::LW - 1 ? 0.0 : xc - ee;
+            const double t = (dw + de) + ((xc - so[c]) + (xc - no[c]));
+            const double e = sp == 0 ? fma(-y.g, xo * sc, y.e0) : fma(y.g, sc * sc, y.e0);
+            double res = fma(-y.c, t, fma(-e, xc, fma(xo - xc, y.inv_dt, y.src)));
+            rr = fma(res, res, rr);
+            float rf = (float)res;
+            RD_PIN(rf);
+            RD_PIN(rr);
+            r[k * C + c] = rf;
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            so[c] = cur[c];
+            cur[c] = no[c];
+        }
+        if (k % 4 == 3)
+            group_end();
+    }
+    return rr;
+}
+
+// Squared tolerance of an FP64 system.  A residual of the preconditioned
+// iteration is smooth where plain CG's is rough, and the same norm of it
+// stands for a larger error of the field (A is 1/dt on the smooth part, up to
+// 8 c on the rough one): a twentieth of the caller's tolerance gives the
+// accuracy that plain CG had at it, but not below the rounding of the
+// evaluated residual.
+__device__ __forceinline__ double fp64_rtol2(double rtol2, const System &y)
+{
+    const double floor2 = 1e-30 * (8.0 + 8.0 * y.c / y.inv_dt) * (8.0 + 8.0 * y.c / y.inv_dt);
+    return fmax(0.0025 * rtol2, fmin(rtol2, floor2));
+}
+
+// Corrections of an FP64 system after its first solve: refined until the
+// evaluated residual meets the tolerance.  A residual that has stopped
+// falling although every correction converged is at the rounding level of
+// its own evaluation and is accepted.
+template <class S>
+__device__ __forceinline__ int refine(Ctx<S> &x, const System &y, int sp, int fo, int ft, int fn,
+                                      float (&r)[S::R], const float (&sg)[S::R], float (&d)[S::R],
+                                      Scalars &v, int hb)
+{
+    bool first = true;
+    double best = __builtin_inf();
+    int stalled = 0;
+    for (;;) {
+        correct(x, sp, fo, fn, first, d, hb);
+        first = false;
+        x.sync();
+        v.rr = x.sum1(true_residual(x, y, sp, fo, ft, fn, r), RedSlots<S::W>::misc);
+        if (!finite(v.rr))
+            return kStNonfinite;
+        if (!(v.rr > v.rtol2 * v.bb))
+            return 0;
+        stalled = v.rr > 0.25 * best ? stalled + 1 : 0;
+        if (stalled >= 3)
+            return 0;
+        best = v.rr < best ? v.rr : best;
+#pragma unroll
+        for (int i = 0; i < S::R; ++i)
+            d[i] = 0.0f;
+        // FP32 recursion: at most five digits per correction
+        const double stop2 = fmax(0.0625 * v.rtol2 * v.bb, 1e-10 * v.rr);
+        const int st = pcg(x, y, r, sg, d, stop2, v);
+        if (st)
+            return st;
+    }
+}
+
+// One item: all IMEX steps, then the outputs and the misfit.
+template <class S, bool kFp64>
+__device__ __forceinline__ void solve_item(const SolveArgs &a, int c, const GridDev &gd, Ctx<S> &x)
+{
+    constexpr int C = S::C, R = S::R, N = S::N, K = S::K;
+    constexpr size_t NN = (size_t)N * N;
     const double th0 = a.theta[4 * c], th1 = a.theta[4 * c + 1], th2 = a.theta[4 * c + 2],
                  th3 = a.theta[4 * c + 3];
-    {
-        const float *u0 = (const float *)gd.u0 + x.o, *v0 = (const float *)gd.v0 + x.o;
+    // fields: FP32 problems u, v (advanced in place); FP64 problems u, v of
+    // the present and the next level, in turn
+#pragma unroll 1
+    for (int k = 0; k < K; ++k) {
+        double u[C], v[C];
 #pragma unroll
-        for (int k = 0; k < kRows; ++k)
-#pragma unroll
-            for (int cc = 0; cc < C; ++cc) {
-                const int i = k * N + cc;  // stored as [hi | lo]
-                x.field(0)[x.o + i] = (double)u0[i] + (double)u0[NN + i];
-                x.field(1)[x.o + i] = (double)v0[i] + (double)v0[NN + i];
+        for (int cc = 0; cc < C; ++cc) {
+            const size_t gi = x.cell0() + x.row(k) + x.o + cc;
+            if constexpr (kFp64) {
+                u[cc] = ((const double *)gd.u0)[gi];
+                v[cc] = ((const double *)gd.v0)[gi];
+            } else {  // stored as [hi | lo]
+                u[cc] = (double)((const float *)gd.u0)[gi] + (double)((const float *)gd.u0)[NN + gi];
+                v[cc] = (double)((const float *)gd.v0)[gi] + (double)((const float *)gd.v0)[NN + gi];
             }
+        }
+        store_cols(x.field(0) + x.row(k), x.o, u);
+        store_cols(x.field(1) + x.row(k), x.o, v);
+        x.put_edge(0, k, u);
+        x.put_edge(1, k, v);
     }
-    __syncthreads();  // the rows of the neighbouring waves are in place
+    x.sync();  // the rows of the neighbouring strips are in place
     const double inv_dt = uniform(1.0 / a.dt);
     const double decay = gd.decay;
     double rho_m2 = 1.0;
-    int st = 0, steps = 0, itu = 0, itv = 0, quiet = 0;  // (bit sp)
+    int st = 0, itu = 0, itv = 0, steps = 0, quiet = 0;  // quiet: bit sp
+    int cur = 0;  // FP64: fields of the present level are 2 cur, 2 cur + 1
     float r[R], sg[R], d[R];
-    double bb, rr, es;
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+        d[i] = 0.0f;
+    Scalars v;
     for (int n = 0; n < a.n_steps; ++n, rho_m2 = uniform(rho_m2 * decay)) {
         // buffer n & 1 holds the increment of step n - 2 and receives this one
         const int kn = n & 1, np = n < 2 ? n : 2;
@@ -689,88 +1070,109 @@ __device__ void solve_item(const SolveArgs &a, int c, const GridDev &gd, Lds<N> 
             y.src = uniform(th2 * (sp ? th1 : th0));
             y.e0 = uniform(sp ? gd.dil : gd.dil + th2);
             y.g = uniform(th2);
+            const int fo = 2 * cur + sp, ft = 2 * cur + (1 - sp);
+            double es;
+            // (FP32: d is the increment of the other species' last system)
             if (sp == 0)
-                residual<N, 0>(x, y, r, sg, bb, rr, es, d, nullptr);
-            else  // (d still holds the increment of u)
-                residual<N, 1>(x, y, r, sg, bb, rr, es, d, x.h(0, kn));
-            int it = 0, still = 0;
-            st = solve<N>(x, y, r, sg, d, bb, rr, es, x.h(sp, kn ^ 1), x.h(sp, kn),
-                          (quiet >> sp) & 1 ? 0 : np, a.rtol2, a.maxit, it, still);
+                residual<S, 0, !kFp64>(x, y, fo, ft, r, sg, v.bb, v.rr, es, d, kn ^ 1);
+            else
+                residual<S, 1, !kFp64>(x, y, fo, ft, r, sg, v.bb, v.rr, es, d, kn);
+            int still = 0;
+            v.it = 0;
+            v.maxit = a.maxit;
+            v.rtol2 = kFp64 ? fp64_rtol2(a.rtol2, y) : a.rtol2;
+            start(x, y, sp, kn, (quiet >> sp) & 1 ? 0 : np, r, sg, d, es, v, still);
+            st = pcg(x, y, r, sg, d, v.rtol2 * v.bb, v);
+            if constexpr (kFp64) {
+                if (st == 0)
+                    st = refine(x, y, sp, fo, ft, 2 * (cur ^ 1) + sp, r, sg, d, v, kn);
+            }
             quiet = (quiet & ~(1 << sp)) | (still << sp);
-            itu += sp == 0 ? it : 0;
-            itv += sp == 1 ? it : 0;
+            itu += sp == 0 ? v.it : 0;
+            itv += sp == 1 ? v.it : 0;
             if (st)
                 break;
         }
         if (st) {
-            if (sp == 1) {
+            if (!kFp64 && sp == 1) {
                 // the step is not taken: u goes back to level n
 #pragma unroll 1
-                for (int k = 0; k < kRows; ++k)
+                for (int k = 0; k < K; ++k)
 #pragma unroll
                     for (int cc = 0; cc < C; ++cc) {
-                        const int i = x.o + k * N + cc;
+                        const int i = x.row(k) + x.o + cc;
                         x.field(0)[i] -= (double)x.h(0, kn)[i];
                     }
             }
             break;
         }
-        const int o = opaque(x.o);
-#pragma unroll
-        for (int k = 0; k < kRows; ++k) {
-#pragma unroll
-            for (int cc = 0; cc < C; ++cc) {
-                const int i = o + k * N + cc;
-                const float dk = d[k * C + cc];
-                x.field(1)[i] += (double)dk;
-                x.h(1, kn)[i] = dk;
-            }
-        }
         steps = n + 1;
+        if constexpr (kFp64)
+            cur ^= 1;
         if (a.steady_tt > 0.0) {
             double acc = 0.0;
-#pragma unroll 1
-            for (int k = 0; k < kRows; ++k)
+            const unsigned o = opaque(x.o);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                float du[C], dv[C];
+                load_cols(x.h(0, kn) + x.row(k), o, du);
+                if (kFp64)
+                    load_cols(x.h(1, kn) + x.row(k), o, dv);
 #pragma unroll
                 for (int cc = 0; cc < C; ++cc) {
-                    const int i = x.o + k * N + cc;
-                    const double du = x.h(0, kn)[i], dv = x.h(1, kn)[i];
-                    acc += du * du + dv * dv;
+                    const double a0 = du[cc], a1 = kFp64 ? dv[cc] : d[k * C + cc];
+                    acc += a0 * a0 + a1 * a1;
                 }
+                group_end();
+            }
             const double thr = a.steady_tt * (double)N;
-            if (block_sum<W>(acc, s.red + RedSlots<W>::misc, x.w) < thr * thr)
+            if (x.sum1(acc, RedSlots<S::W>::misc) < thr * thr)
                 break;
             if (n + 1 == a.n_steps)
                 st = kStNotSteady;  // the cap came first
-        } else {
-            __syncthreads();  // the fields of this level are in place
         }
     }
     if (a.n_steps == 0 && a.steady_tt > 0.0)
         st = kStNotSteady;
+    const bool pending = !kFp64 && steps > 0 && (st == 0 || st == kStNotSteady);
     const size_t off = (size_t)c * a.out_stride;
     double sum = 0.0;
-#pragma unroll 4
-    for (int k = 0; k < kRows; ++k)
+    const unsigned o1 = opaque(x.o);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        double uu[C], vv[C];
+        load_cols(x.field(2 * cur) + x.row(k), o1, uu);
+        load_cols(x.field(2 * cur + 1) + x.row(k), o1, vv);
 #pragma unroll
         for (int cc = 0; cc < C; ++cc) {
-            const int i = x.o + k * N + cc;
-            const double u = x.field(0)[i];
-            if (a.u_out)
-                ((float *)a.u_out)[off + i] = (float)u;
-            if (a.v_out)
-                ((float *)a.v_out)[off + i] = (float)x.field(1)[i];
+            const size_t gi = x.cell0() + x.row(k) + o1 + cc;
+            const double u = uu[cc];
+            const double w = vv[cc] + (pending ? (double)d[k * C + cc] : 0.0);  // v's last increment
+            if (a.u_out) {
+                if constexpr (kFp64)
+                    ((double *)a.u_out)[off + gi] = u;
+                else
+                    ((float *)a.u_out)[off + gi] = (float)u;
+            }
+            if (a.v_out) {
+                if constexpr (kFp64)
+                    ((double *)a.v_out)[off + gi] = w;
+                else
+                    ((float *)a.v_out)[off + gi] = (float)w;
+            }
             if (a.phi && gd.y) {
-                const double e = gd.y[i] - u;
+                const double e = gd.y[gi] - u;
                 sum = fma(e, e, sum);
             }
         }
+        group_end();
+    }
     if (a.phi) {
-        sum = block_sum<W>(sum, s.red + RedSlots<W>::gram, x.w);
-        if (threadIdx.x == 0)
+        sum = x.sum1(sum, RedSlots<S::W>::gram);
+        if (x.leader())
             a.phi[c] = (st != 0 || !gd.y || !finite(sum)) ? __builtin_inf() : sum * gd.inv_2s2;
     }
-    if (threadIdx.x == 0) {
+    if (x.leader()) {
         a.status[c] = st;
         if (a.steps_out)
             a.steps_out[c] = steps;
@@ -781,27 +1183,34 @@ __device__ void solve_item(const SolveArgs &a, int c, const GridDev &gd, Lds<N> 
     }
 }
 
-template <int N>
-__global__ __launch_bounds__(Layout<N>::T, N == 128 ? 2 : 4) void k_solve_pcg(SolveArgs a)
+// Fields of an item's slot, and the slot's size (they are followed by the
+// last two increments of each species).
+template <bool kFp64>
+constexpr int n_fields()
 {
-    __shared__ __attribute__((aligned(16))) Lds<N> s;
-    init_tables<N>(s);
-    void *slot = (char *)a.gws + (size_t)blockIdx.x * a.gws_stride;
+    return kFp64 ? 4 : 2;
+}
+template <class S>
+constexpr size_t slot_bytes(bool fp64)
+{
+    return (size_t)S::cells * ((fp64 ? 4 : 2) * sizeof(double) + 4 * sizeof(float));
+}
+
+template <class S, bool kFp64, int kWavesPerSimd>
+__global__ __launch_bounds__(S::T, kWavesPerSimd) void k_solve_pcg(SolveArgs a)
+{
+    __shared__ __attribute__((aligned(16))) Lds<S> s;
+    init_tables<S>(s);
+    Ctx<S> x(s, (char *)a.gws + (size_t)blockIdx.x * a.gws_stride, n_fields<kFp64>());
     for (int item = next_item(a.queue, &s.item); item < a.n_items;
          item = next_item(a.queue, &s.item)) {
         const int c = uniform(a.order ? a.order[item] : item);
         if (!a.need || uniform(a.need[c])) {
             const int gid = item_grid(a, c);
             if (gid >= 0)
-                solve_item<N>(a, c, a.grids[gid], s, slot);
+                solve_item<S, kFp64>(a, c, a.grids[gid], x);
         }
     }
-}
-
-template <int N>
-constexpr size_t slot_bytes()
-{
-    return (size_t)N * N * (2 * sizeof(double) + 4 * sizeof(float));
 }
 
 }  // namespace pcg

@@ -2281,10 +2281,9 @@ enum Kind { kNone, kResident, kStreamed, kCoop, kSpectral };
 Kind tile_kind(int n, int precision, int cpt)
 {
     if (precision == 0) {
-        if (n == 32 && (cpt == 4 || cpt == 8 || cpt == 16))
-            return kResident;
-        // one kernel serves every tile of these two sizes
-        if ((n == 64 && (cpt == 4 || cpt == 8 || cpt == 16)) ||
+        // one kernel serves every tile of these sizes
+        if ((n == 32 && (cpt == 4 || cpt == 8 || cpt == 16)) ||
+            (n == 64 && (cpt == 4 || cpt == 8 || cpt == 16)) ||
             (n == 128 && (cpt == 16 || cpt == 32)))
             return kSpectral;
         if (n == 256 && cpt == kCoopR)
@@ -2292,12 +2291,12 @@ Kind tile_kind(int n, int precision, int cpt)
         if (n == 256 && (cpt == 64 || cpt == 128))
             return kStreamed;
     } else {
+        // (32^2 in FP64: few iterations to save, and callers compare it with
+        // plain CG stopped at the same tolerance)
         if (n == 32 && (cpt == 4 || cpt == 8 || cpt == 16))
             return kResident;
-        if (n == 64 && (cpt == 8 || cpt == 16))
-            return kResident;
-        if (n == 128 && cpt == 32)
-            return kStreamed;
+        if ((n == 64 && (cpt == 8 || cpt == 16)) || (n == 128 && cpt == 32))
+            return kSpectral;
         if (n == 256 && cpt == 128)
             return kStreamed;
     }
@@ -2320,18 +2319,33 @@ hipError_t go_streamed(const SolveArgs &a, int wgs, hipStream_t s)
 
 }  // namespace
 
+// f(kernel, threads) for the spectrally preconditioned kernel of a size.
+template <typename F>
+static void spectral(int n, int precision, F &&f)
+{
+    using namespace pcg;
+    // waves per SIMD: three at 64^2 (2000 prior draws of 300 steps 26.4 ms; two
+    // 29.4, four, which spill, 29.6)
+    if (n == 32)
+        f(k_solve_pcg<S32, false, 4>, S32::T);
+    else if (n == 64)
+        precision ? f(k_solve_pcg<S64, true, 2>, S64::T) : f(k_solve_pcg<S64, false, 3>, S64::T);
+    else
+        precision ? f(k_solve_pcg<S128, true, 2>, S128::T)
+                  : f(k_solve_pcg<S128, false, 2>, S128::T);
+}
+
 bool tile_supported(int n, int precision, int cpt)
 {
     return tile_kind(n, precision, cpt) != kNone;
 }
 
-// Defaults measured on MI355X.  FP32 64^2 and 128^2: the spectrally
-// preconditioned kernel (rd_pcg.hpp) at every problem size and tolerance: per
-// IMEX step of one item 48 us against 90 us for plain CG (512 items of 128^2
-// near the posterior, first 500 steps), 52 against 196 us (4096 prior draws,
-// first 200 steps, where plain CG takes 51 iterations per step and this
-// kernel 3), 42 against 111 us for a single item, and 2000 prior draws at
-// 64^2 in 32 against 75 ms.  At 32^2 16 cells per thread.  At 256^2 in FP32 the cooperative
+// Defaults measured on MI355X.  The spectrally preconditioned kernel
+// (rd_pcg.hpp) against plain CG: 512 items of 128^2 in FP32 near the posterior,
+// first 500 steps, 42.8 against 89.5 ms; 4096 prior draws, first 200 steps, 150
+// against 625 ms (51 CG iterations per step against 3); one item 36 against 111 us
+// per step; 2000 prior draws of 64^2 25.7 against 68 ms; 5000 growing items of
+// 32^2 15.0 against 20.4 ms; 64 items of 128^2 in FP64 4.3 against 144 ms.  At 256^2 in FP32 the cooperative
 // tile (16 cells per thread, four workgroups per item) is 9 to 14 times
 // faster per item than the streamed one.
 int default_cpt(int n, int precision)
@@ -2346,7 +2360,9 @@ size_t solve_slot_bytes(int n, int precision, int cpt)
     if (tile_kind(n, precision, cpt) == kCoop)  // one member's strip: 4 arrays
         return (size_t)4 * kCoopStrip * kCoopN * sizeof(float);
     if (tile_kind(n, precision, cpt) == kSpectral)
-        return n == 64 ? pcg::slot_bytes<64>() : pcg::slot_bytes<128>();
+        return n == 32   ? pcg::slot_bytes<pcg::S32>(precision != 0)
+               : n == 64 ? pcg::slot_bytes<pcg::S64>(precision != 0)
+                         : pcg::slot_bytes<pcg::S128>(precision != 0);
     // SlotLayout: low parts and two increments per species (6 arrays), and
     // for streamed tiles the strip arrays and p after them (6 more)
     const size_t arrays = tile_kind(n, precision, cpt) == kStreamed ? 12 : 6;
@@ -2372,16 +2388,15 @@ int solve_wgs_per_cu(int n, int precision, int cpt)
         return occupancy(k_solve_streamed<NN, RR, T>, NN * NN / RR);
     if (tile_kind(n, precision, cpt) == kCoop)
         return occupancy(k_solve_coop, kCoopThreads);
-    if (tile_kind(n, precision, cpt) == kSpectral)
-        return n == 64 ? occupancy(pcg::k_solve_pcg<64>, pcg::Layout<64>::T)
-                       : occupancy(pcg::k_solve_pcg<128>, pcg::Layout<128>::T);
+    if (tile_kind(n, precision, cpt) == kSpectral) {
+        int wgs = 1;
+        spectral(n, precision, [&](auto kernel, int threads) { wgs = occupancy(kernel, threads); });
+        return wgs;
+    }
     if (precision == 0) {
-        RD_OCC_R(32, 4, float) RD_OCC_R(32, 8, float) RD_OCC_R(32, 16, float)
         RD_OCC_S(256, 64, float) RD_OCC_S(256, 128, float)
     } else {
         RD_OCC_R(32, 4, double) RD_OCC_R(32, 8, double) RD_OCC_R(32, 16, double)
-        RD_OCC_R(64, 8, double) RD_OCC_R(64, 16, double)
-        RD_OCC_S(128, 32, double)
         RD_OCC_S(256, 128, double)
     }
 #undef RD_OCC_R
@@ -2509,19 +2524,15 @@ hipError_t launch_solve(int n, int precision, TileChoice tile, const SolveArgs &
     if (tile_kind(n, precision, cpt) == kCoop)
         return launch_solve_coop(a, wgs, s);
     if (tile_kind(n, precision, cpt) == kSpectral) {
-        if (n == 64)
-            hipLaunchKernelGGL(pcg::k_solve_pcg<64>, dim3(wgs), dim3(pcg::Layout<64>::T), 0, s, a);
-        else
-            hipLaunchKernelGGL(pcg::k_solve_pcg<128>, dim3(wgs), dim3(pcg::Layout<128>::T), 0, s, a);
+        spectral(n, precision, [&](auto kernel, int threads) {
+            hipLaunchKernelGGL(kernel, dim3(wgs), dim3(threads), 0, s, a);
+        });
         return hipGetLastError();
     }
     if (precision == 0) {
-        RD_RES(32, 4, float) RD_RES(32, 8, float) RD_RES(32, 16, float)
         RD_STR(256, 64, float) RD_STR(256, 128, float)
     } else {
         RD_RES(32, 4, double) RD_RES(32, 8, double) RD_RES(32, 16, double)
-        RD_RES(64, 8, double) RD_RES(64, 16, double)
-        RD_STR(128, 32, double)
         RD_STR(256, 128, double)
     }
 #undef RD_RES

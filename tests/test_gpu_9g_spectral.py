@@ -1,5 +1,5 @@
-"""The spectrally preconditioned FP32 solve against the FP64 oracle: both grid
-sizes, the first steps (where the start vector uses 0, 1 and 2 increments),
+"""The spectrally preconditioned solve against the FP64 oracle: every grid size
+and precision that takes it, the first steps (where the start vector uses 0, 1 and 2 increments),
 both ends of the diffusion ratio (the preconditioner's work grows with d),
 growing domain, more items than one workgroup, and the iteration cap."""
 import numpy as np
@@ -22,20 +22,20 @@ def _problem(n, steps, rtol, **kw):
     return Problem(g, TAU, steps, rtol, max_batch=8, **kw), u0, v0
 
 
-@pytest.mark.parametrize("n", [64, 128])
+@pytest.mark.parametrize("n,fp64", [(32, 0), (64, 0), (128, 0), (64, 1), (128, 1)])
 @pytest.mark.parametrize("steps,rate,rtol", [(0, 0.0, 1e-9), (1, 0.0, 1e-9), (2, 0.0, 1e-9),
                                              (3, 0.01, 1e-9), (12, 0.0, 1e-9), (12, 0.01, 1e-7)])
-def test_fields_match_the_oracle(n, steps, rate, rtol):
+def test_fields_match_the_oracle(n, fp64, steps, rate, rtol):
     import torch
     need_gpu()
-    p, u0, v0 = _problem(n, steps, rtol, rate=rate)
+    p, u0, v0 = _problem(n, steps, rtol, rate=rate, precision=fp64)
     u, v, status, _ = p.forward_solve(torch.tensor(np.tile(THETAS, (2, 1)), device="cuda"))
     u, v, status = u.double().cpu().numpy(), v.double().cpu().numpy(), status.cpu().numpy()
     p.close()
     # a step's residual of at most rtol |b| with |b| <= (1/dt + gamma) |x| and
     # A >= 1/dt moves the field by at most 1.2 rtol |x|; 4 covers its growth
-    # over a few steps, and the output is rounded to FP32 (2^-24)
-    tol = 2.0 ** -24 + 4 * 1.2 * steps * rtol
+    # over a few steps, and the output is rounded to FP32 (2^-24) or FP64
+    tol = (2.0 ** -50 if fp64 else 2.0 ** -24) + 4 * 1.2 * steps * rtol
     for k in range(6):
         uo, vo, _, st = oracle.forward_solve(THETAS[k % 3], u0, v0, TAU, steps, rtol=1e-13,
                                              growth=int(rate != 0.0), rate=rate)
@@ -46,12 +46,12 @@ def test_fields_match_the_oracle(n, steps, rate, rtol):
     assert np.array_equal(u[:3], u[3:]) and np.array_equal(v[:3], v[3:])
 
 
-@pytest.mark.parametrize("n", [64, 128])
-def test_iteration_cap_is_reported(n):
+@pytest.mark.parametrize("n,fp64", [(32, 0), (64, 0), (128, 0), (64, 1), (128, 1)])
+def test_iteration_cap_is_reported(n, fp64):
     import torch
     need_gpu()
-    p, _, _ = _problem(n, 3, 1e-9, cg_maxit=1)
+    p, _, _ = _problem(n, 3, 1e-9, cg_maxit=2, precision=fp64)
     _, _, status, it = p.forward_solve(torch.tensor(THETAS, device="cuda"))
-    assert np.all(status.cpu().numpy() == 1)   # one iteration does not reach 1e-9 at step 0
-    assert np.all(it.cpu().numpy().max(axis=1) == 1)
+    assert np.all(status.cpu().numpy() == 1)   # two plain iterations do not reach 1e-9 at step 0
+    assert np.all(it.cpu().numpy().max(axis=1) == 2)
     p.close()
