@@ -100,7 +100,8 @@ typedef struct {
     double dt;                     /* time step tau */
     int32_t n_steps;               /* T = dt * n_steps */
     double cg_rtol;                /* CG stop: ||r|| <= cg_rtol ||rhs|| */
-    int32_t cg_maxit;              /* CG iteration cap per solve (<= 0: 10 n^2) */
+    int32_t cg_maxit;              /* CG iteration cap per solve (<= 0: 10 n^2); below 16 the
+                                    * iterations run without the preconditioner */
     int32_t precision;             /* RD_PRECISION_FP32: fields (as hi + lo) and CG
                                       vectors in FP32, the CG step lengths in
                                       FP32 from FP64 dot products, Phi in FP64.
@@ -390,26 +391,23 @@ int32_t surrogate_params(rd_problem *p, int32_t layer, float *w, float *b, int32
 
 /* Re-runs the tile-shape autotuner for every grid class of p (a few timed
  * trial solves) and keeps the fastest; returns the chosen cells-per-thread
- * of each class in cpt_out (host int32 [n_grids], may be NULL).  With
- * several grid classes it also times the mixed-class launch at 512 and 1024
- * threads per workgroup and keeps the faster (see rd_mixed_threads).  The
- * choice is cached per device, grid size and precision for later problems. */
+ * of each class in cpt_out (host int32 [n_grids], may be NULL).  The choice
+ * is cached per device, grid size and precision for later problems. */
 int32_t rd_autotune(rd_problem *p, int32_t *cpt_out);
 
 /* Selects the tile of grid class `grid` by its cells per thread (the value
  * rd_autotune reports), overriding the default and any cached choice for
  * this problem only.  Supported values depend on the grid size and
- * precision; at 256 x 256 in FP32, cpt = 16 selects the cooperative tile
- * (four workgroups share an item, each holding a 64-row strip resident).
+ * precision; at 256 x 256, cpt = 32 (the default) selects the
+ * preconditioned solve by a group of four workgroups, in FP32 cpt = 16 the
+ * group's plain CG, and the others the single-workgroup streamed plain CG.
  * Errors: RD_EINVAL (NULL problem, grid out of range), RD_EUNSUPPORTED (no
  * kernel for that cpt at this size and precision). */
 int32_t rd_set_tile(rd_problem *p, int32_t grid, int32_t cpt);
 
-/* Sets the workgroup size (512 or 1024) of the launch that serves batches
- * mixing grid classes, overriding the default and any cached choice for
- * this problem only.  With 1024 and 256 x 256 FP32 classes, one launch
- * serves all classes (the 256 x 256 items by groups of four workgroups);
- * with 512 a cooperative launch for those items precedes the mixed launch.
+/* Sets the nominal workgroup size (512 or 1024) of batches mixing grid
+ * classes, for this problem only.  Every grid size has one workgroup shape
+ * of its own now, so both values launch the same kernels.
  * Errors: RD_EINVAL (NULL problem, other sizes). */
 int32_t rd_set_mixed_threads(rd_problem *p, int32_t threads);
 

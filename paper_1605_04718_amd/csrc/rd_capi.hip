@@ -119,10 +119,11 @@ struct rd_problem {
     std::vector<void *> allocs;
     TileChoice tile[RD_MAX_GRIDS]{};
     int wgs_per_cu[RD_MAX_GRIDS]{};  // resident workgroups per CU of tile[g]
-    // batches that mix grid classes: one persistent launch of this many
-    // threads per workgroup, queue ordered by class cost
-    int mixed_threads = 1024;
-    int mixed_wpc = 1;
+    // batches that mix grid classes: a queue ordered by class cost, one launch
+    // for the 256^2 and 128^2 items and one for each smaller size
+    int mixed_threads = 1024;  // (512 or 1024; every size has one workgroup shape)
+    int class_wpc[2] = {1, 1};  // workgroups per CU of the 64^2 and 32^2 launches
+    bool has_n[4] = {false, false, false, false};  // classes of 256, 128, 64, 32 cells a side
     RankTable rank{};
     int *order_ws = nullptr;
     int maxit = 0;
@@ -154,7 +155,10 @@ struct rd_problem {
     void *coop = nullptr;    // cooperative-solve workspace (256^2 FP32)
     int coop_groups = 0;
     int coop_wpc = 0;        // resident cooperative workgroups per CU
-    int mixed_coop_wpc = 0;  // resident workgroups per CU of the fused mixed launch
+    void *group_ws = nullptr;  // workspace of the spectral 256^2 groups
+    int group_cap = 0;
+    TileChoice noalloc_tile{};  // streamed tile of a 256^2 FP64 problem
+    int noalloc_wpc = 0;
     // cooperative waits: bound (100 MHz ticks), test-hook stall, and the
     // device count of members whose wait gave up since the last check
     unsigned long long coop_wait_ticks = 1000000000ull;
@@ -266,6 +270,8 @@ struct SolveWs {
     void *gws;
     size_t stride;
     int slots;
+    TileChoice tile;
+    int wgs_per_cu;
 };
 
 int32_t enqueue_solve(rd_problem *p, int n, const double *theta, const int *grid_id,
@@ -303,6 +309,8 @@ int32_t enqueue_solve(rd_problem *p, int n, const double *theta, const int *grid
     a.gws_slots = p->gws_slots;
     a.coop = p->coop;
     a.coop_groups = p->coop_groups;
+    a.group_ws = p->group_ws;
+    a.group_cap = p->group_cap;
     a.steady_tt = p->desc.steady_tol > 0.0 ? p->desc.steady_tol * p->desc.dt : 0.0;
     a.steps_out = steps_out;
     a.coop_wait_ticks = p->coop_wait_ticks;
@@ -315,38 +323,22 @@ int32_t enqueue_solve(rd_problem *p, int n, const double *theta, const int *grid
         a.gws_slots = ws->slots;
         a.coop = nullptr;
         a.coop_groups = 0;
+        a.group_ws = nullptr;
+        a.group_cap = 0;
     }
-    const TileChoice t = p->tile[g];
+    const TileChoice t = ws ? ws->tile : p->tile[g];
     // wgs_per_cu was queried when the tile was chosen: no runtime query may
     // run here, since this is also called while a stream is being captured.
-    int wgs = p->n_cu * (mixed ? p->mixed_wpc : p->wgs_per_cu[g]);
+    int wgs = p->n_cu * (ws ? ws->wgs_per_cu : p->wgs_per_cu[g]);
     if (ws) {
         if (mixed || cost || tile_coop(nn, p->desc.precision, t.cpt))
             return fail(RD_EUNSUPPORTED, "external workspace: single-class, uncooperative tiles only");
         wgs = std::min(wgs, ws->slots);
     }
     // (a cooperative tile sizes its grid from the item count itself)
-    if (wgs > n && (mixed || !tile_coop(nn, p->desc.precision, t.cpt)))
+    if (wgs > n && !tile_coop(nn, p->desc.precision, t.cpt))
         wgs = n;
-    // batches mixing classes with 256^2 FP32 items: groups of four resident
-    // workgroups serve them (the prefix of the class-ordered queue).  With
-    // 1024-thread workgroups one launch does both (the cooperative
-    // workgroups join the other classes' queue when the prefix is done);
-    // with 512 a cooperative launch runs first and the mixed launch skips
-    // the 256^2 items.
-    a.coop_wgs = 0;
-    int coop_grid = 0;
-    const bool fused = p->mixed_threads == kCoopThreads;
-    if (mixed && p->coop && p->desc.precision == 0) {
-        // every workgroup of the fused launch is resident at once, and the
-        // cooperative role takes whole blocks of 32 (small batches too)
-        if (fused)
-            wgs = std::min(std::max(wgs, 32), p->n_cu * p->mixed_coop_wpc);
-        coop_grid = std::min((fused ? wgs : p->n_cu * p->coop_wpc) / 32 * 32,
-                             p->coop_groups * kCoopG);
-        a.coop_wgs = coop_grid >= 32 ? coop_grid : 0;
-    }
-    HIP_TRY(launch_fill_u32(a.queue, 0u, 1, s));
+    HIP_TRY(launch_fill_u32(a.queue, 0u, mixed ? 3 : 1, s));
     if (mixed) {
         HIP_TRY(launch_class_order(grid_id, n, p->desc.n_grids, p->rank, p->order_ws, s));
         a.order = p->order_ws;
@@ -359,12 +351,28 @@ int32_t enqueue_solve(rd_problem *p, int n, const double *theta, const int *grid
         HIP_TRY(record_solve_start(p, s, &e0));
     if (!mixed) {
         HIP_TRY(launch_solve(nn, p->desc.precision, t, a, wgs, s));
-    } else if (a.coop_wgs && fused) {
-        HIP_TRY(launch_solve_mixed_coop(a, wgs, s));
     } else {
-        if (a.coop_wgs)
-            HIP_TRY(launch_solve_coop(a, coop_grid, s));
-        HIP_TRY(launch_solve_mixed(p->desc.precision, p->mixed_threads, a, wgs, s));
+        // One launch for the 256^2 prefix of the queue (groups of four
+        // workgroups) and the 128^2 items, which its workgroups take over when
+        // the prefix is done; then the small sizes, whose workgroups are
+        // smaller and share a CU.  Each launch has a queue head of its own and
+        // passes over the other sizes.
+        const int prec = p->desc.precision;
+        unsigned *queue = a.queue;
+        if (p->has_n[0] || p->has_n[1]) {
+            int big = std::min(p->n_cu, p->gws_slots) / 32 * 32;
+            big = std::min(big, (n * kCoopG + 31) / 32 * 32);
+            a.coop_wgs = p->has_n[0] ? std::min(big, p->group_cap * kCoopG / 32 * 32) : 0;
+            HIP_TRY(launch_solve_group(prec, a, big, true, s));
+        }
+        a.coop_wgs = 0;
+        for (int k = 0; k < 2; ++k) {
+            if (!p->has_n[2 + k])
+                continue;
+            a.queue = queue + 1 + k;
+            const int most = std::min(p->n_cu * p->class_wpc[k], p->gws_slots);
+            HIP_TRY(launch_solve_class(k == 0 ? 64 : 32, prec, a, std::min(most, n), s));
+        }
     }
     HIP_TRY(record_solve_end(p, s, e0));
     return RD_OK;
@@ -606,6 +614,10 @@ extern "C" int32_t init_problem(const rd_problem_desc *desc, rd_problem **out)
         p->tile[g] = TileChoice{cpt, nn / cpt};
         p->wgs_per_cu[g] = solve_wgs_per_cu(gd.n, desc->precision, cpt);
     }
+    if (desc->precision == RD_PRECISION_FP64 && desc->n_grids == 1 && max_n == 256) {
+        p->noalloc_tile = TileChoice{128, 256 * 256 / 128};
+        p->noalloc_wpc = solve_wgs_per_cu(256, desc->precision, 128);
+    }
     p->maxit = desc->cg_maxit > 0 ? desc->cg_maxit : 10 * max_n * max_n;
     p->max_n = max_n;
     const int B = desc->max_batch;
@@ -660,12 +672,6 @@ extern "C" int32_t init_problem(const rd_problem_desc *desc, rd_problem **out)
                 slots = std::max(slots, p->n_cu * solve_wgs_per_cu(n, desc->precision, cpt));
             }
         }
-        if (desc->n_grids > 1) {
-            for (int threads : {512, 1024}) {
-                slot = std::max(slot, mixed_slot_bytes(n, desc->precision, threads));
-                slots = std::max(slots, p->n_cu * mixed_wgs_per_cu(desc->precision, threads));
-            }
-        }
     }
     if (desc->n_grids > 1) {
         // queue order: larger grids first (cost per solve ~ cells)
@@ -677,21 +683,29 @@ extern "C" int32_t init_problem(const rd_problem_desc *desc, rd_problem **out)
         });
         for (int k = 0; k < desc->n_grids; ++k)
             p->rank.r[cls[k]] = k;
-        {
-            std::lock_guard<std::mutex> lk(g_tune_mu);
-            auto it = g_tuned.find(tune_key(p->device, -1, desc->precision));
-            if (it != g_tuned.end())
-                p->mixed_threads = it->second;
-        }
-        p->mixed_wpc = mixed_wgs_per_cu(desc->precision, p->mixed_threads);
+        for (int g = 0; g < desc->n_grids; ++g)
+            for (int k = 0; k < 4; ++k)
+                p->has_n[k] = p->has_n[k] || p->grids_host[g].n == 256 >> k;
+        for (int k = 0; k < 2; ++k)
+            p->class_wpc[k] = solve_wgs_per_cu(64 >> k, desc->precision,
+                                               default_cpt(64 >> k, desc->precision));
+        // (the 128^2 items run in slots of the 256^2 kernel's workgroups)
+        slot = std::max(slot, solve_slot_bytes(256, desc->precision, kGroupCpt));
+        slots = std::max(slots, p->n_cu);
     }
     // cooperative tiles: group counters, partial sums and edge rows
     for (int g = 0; g < desc->n_grids; ++g) {
         const int n = p->grids_host[g].n;
         for (int cpt : {4, 8, 16, 32, 64, 128}) {
-            if (tile_coop(n, desc->precision, cpt) && !p->coop) {
+            if (tile_coop(n, desc->precision, cpt) && cpt == kGroupCpt && !p->group_ws) {
+                p->group_cap = p->n_cu / kCoopG + 8;
+                p->group_ws = dmalloc(p, group_workspace_bytes(p->group_cap), &err);
+                if (p->group_ws &&
+                    (launch_group_tables(p->group_ws, p->group_cap, nullptr) != hipSuccess ||
+                     hipDeviceSynchronize() != hipSuccess))
+                    err = fail(RD_EHIP, "tables of the 256 x 256 groups failed");
+            } else if (tile_coop(n, desc->precision, cpt) && cpt != kGroupCpt && !p->coop) {
                 p->coop_wpc = solve_wgs_per_cu(n, desc->precision, cpt);
-                p->mixed_coop_wpc = mixed_coop_wgs_per_cu();
                 p->coop_groups = p->n_cu * p->coop_wpc / kCoopG + 8;
                 p->coop = dmalloc(p, coop_workspace_bytes(p->coop_groups), &err);
             }
@@ -795,7 +809,10 @@ extern "C" int32_t log_likelihood_batch_noalloc(rd_problem *p, int32_t n, const 
     if (!p->grids_host[0].y)
         return fail(RD_EINVAL, "grid 0 has no data y");
     const int nn = p->grids_host[0].n;
-    const TileChoice t = p->tile[0];
+    // (the default 256^2 tile in FP64 needs the group workspace: the streamed
+    // one takes its place)
+    const bool streamed = p->noalloc_wpc && tile_coop(nn, p->desc.precision, p->tile[0].cpt);
+    const TileChoice t = streamed ? p->noalloc_tile : p->tile[0];
     if (tile_coop(nn, p->desc.precision, t.cpt))
         return fail(RD_EUNSUPPORTED,
                     "log_likelihood_batch_noalloc: the cooperative %dx%d tile needs the problem's "
@@ -811,7 +828,8 @@ extern "C" int32_t log_likelihood_batch_noalloc(rd_problem *p, int32_t n, const 
     if (n == 0)
         return RD_OK;
     SolveWs ws{(unsigned *)p->scratch, (char *)p->scratch + kNoAllocHeader, stride,
-               (int)std::min<size_t>(slots, (size_t)1 << 20)};
+               (int)std::min<size_t>(slots, (size_t)1 << 20), t,
+               streamed ? p->noalloc_wpc : p->wgs_per_cu[0]};
     return enqueue_solve(p, n, theta, nullptr, nullptr, phi, status, cg_iters, nullptr, nullptr,
                          (hipStream_t)stream, 0, nullptr, nullptr, &ws);
 }
@@ -1171,77 +1189,6 @@ extern "C" int32_t rd_autotune(rd_problem *p, int32_t *cpt_out)
         if (cpt_out)
             cpt_out[g] = best;
     }
-    if (p->desc.n_grids > 1) {
-        // Mixed launch: workgroup size, on a batch that cycles through the
-        // classes (one item per workgroup slot).
-        const int trial_steps = std::min(p->desc.n_steps, 160);
-        int best = p->mixed_threads;
-        float best_ms = 1e30f;
-        for (int threads : {512, 1024}) {
-            const int wpc = mixed_wgs_per_cu(p->desc.precision, threads);
-            const int items = std::min(p->desc.max_batch, p->n_cu * wpc);
-            std::vector<double> th(4 * items);
-            std::vector<int> gid(items);
-            for (int k = 0; k < items; ++k) {
-                trial_theta(p->desc, k, &th[4 * k]);
-                gid[k] = k % p->desc.n_grids;
-            }
-            double *d_th = nullptr;
-            int *d_st = nullptr, *d_gid = nullptr;
-            HIP_TRY(hipMalloc(&d_th, sizeof(double) * th.size()));
-            HIP_TRY(hipMalloc(&d_st, sizeof(int) * items));
-            HIP_TRY(hipMalloc(&d_gid, sizeof(int) * items));
-            HIP_TRY(hipMemcpy(d_th, th.data(), sizeof(double) * th.size(), hipMemcpyHostToDevice));
-            HIP_TRY(hipMemcpy(d_gid, gid.data(), sizeof(int) * items, hipMemcpyHostToDevice));
-            const int saved_threads = p->mixed_threads, saved_wpc = p->mixed_wpc;
-            const int saved_steps = p->desc.n_steps;
-            p->mixed_threads = threads;
-            p->mixed_wpc = wpc;
-            p->desc.n_steps = trial_steps;
-            const bool saved_timing = p->timing;
-            p->timing = false;
-            hipEvent_t e0, e1;
-            hipEventCreate(&e0);
-            hipEventCreate(&e1);
-            int32_t r = enqueue_solve(p, items, d_th, d_gid, nullptr, nullptr, d_st, nullptr,
-                                      nullptr, nullptr, nullptr);
-            hipEventRecord(e0, nullptr);
-            if (r == RD_OK)
-                r = enqueue_solve(p, items, d_th, d_gid, nullptr, nullptr, d_st, nullptr, nullptr,
-                                  nullptr, nullptr);
-            hipEventRecord(e1, nullptr);
-            hipEventSynchronize(e1);
-            float ms = 0.f;
-            hipEventElapsedTime(&ms, e0, e1);
-            p->timing = saved_timing;
-            p->desc.n_steps = saved_steps;
-            p->mixed_threads = saved_threads;
-            p->mixed_wpc = saved_wpc;
-            hipEventDestroy(e0);
-            hipEventDestroy(e1);
-            hipFree(d_th);
-            hipFree(d_st);
-            hipFree(d_gid);
-            if (r != RD_OK)
-                return r;
-            float per_item = ms / (float)items;
-            if (getenv("RDBAYES_AUTOTUNE_VERBOSE"))
-                fprintf(stderr, "[rd_autotune] mixed prec=%d threads=%d wgs/cu=%d: %.4f ms/item\n",
-                        p->desc.precision, threads, wpc, per_item);
-            if (threads == p->mixed_threads)
-                per_item *= 1.0f - kTuneMargin;  // incumbent
-            if (per_item < best_ms) {
-                best_ms = per_item;
-                best = threads;
-            }
-        }
-        p->mixed_threads = best;
-        p->mixed_wpc = mixed_wgs_per_cu(p->desc.precision, best);
-        {
-            std::lock_guard<std::mutex> lk(g_tune_mu);
-            g_tuned[tune_key(p->device, -1, p->desc.precision)] = best;
-        }
-    }
     drop_graphs(p);
     return RD_OK;
 }
@@ -1269,7 +1216,6 @@ extern "C" int32_t rd_set_mixed_threads(rd_problem *p, int32_t threads)
     if (threads != 512 && threads != 1024)
         return fail(RD_EINVAL, "threads must be 512 or 1024, got %d", threads);
     p->mixed_threads = threads;
-    p->mixed_wpc = mixed_wgs_per_cu(p->desc.precision, threads);
     drop_graphs(p);  // captured steps launch with the shape of their capture
     return RD_OK;
 }

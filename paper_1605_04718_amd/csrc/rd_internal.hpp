@@ -60,9 +60,9 @@ struct SolveArgs {
     int coop_groups;         // groups the workspace holds
     double steady_tt;        // steady-state stopping: threshold x dt (0: fixed horizon)
     int *steps_out;          // [n] IMEX steps taken (null: skip)
-    int coop_wgs;            // class-ordered batch: nonzero when a cooperative
-                             // launch serves the 256^2 items (the mixed launch
-                             // then skips them)
+    void *group_ws;          // workspace of the 256^2 groups, or null
+    int group_cap;           // groups it holds
+    int coop_wgs;            // leading workgroups of the launch that form groups
     unsigned long long coop_wait_ticks;   // bound of a group wait (100 MHz ticks)
     unsigned long long coop_stall_ticks;  // test hook: member 1 of every group
                                           // sleeps this long first (0: off)
@@ -75,8 +75,16 @@ constexpr int kCoopG = 4;         // workgroups per item (horizontal strips of 6
 constexpr int kCoopThreads = 1024;
 __host__ __device__ size_t coop_workspace_bytes(int groups);
 hipError_t launch_solve_coop(const SolveArgs &a, int grid_wgs, hipStream_t s);
-hipError_t launch_solve_mixed_coop(const SolveArgs &a, int grid_wgs, hipStream_t s);
-int mixed_coop_wgs_per_cu();
+
+// Spectrally preconditioned solve of 256^2 items by groups of four
+// workgroups; `mixed`: the prefix of a class-ordered batch, whose 128^2 items
+// the same launch serves after it (a.coop_wgs workgroups form the groups).
+constexpr int kGroupCpt = 32;  // its tile (cells per thread)
+size_t group_workspace_bytes(int groups);
+hipError_t launch_group_tables(void *ws, int groups, hipStream_t s);
+hipError_t launch_solve_group(int precision, SolveArgs a, int wgs, bool mixed, hipStream_t s);
+// The 32^2 or 64^2 items of a class-ordered batch.
+hipError_t launch_solve_class(int n, int precision, const SolveArgs &a, int wgs, hipStream_t s);
 
 // Class ranks of a mixed batch (queue order: rank 0 first).
 constexpr int kMaxClasses = 8;
@@ -93,8 +101,6 @@ struct TileChoice {
 // Host launchers (rd_solver.hip).
 hipError_t launch_solve(int n, int precision, TileChoice tile, const SolveArgs &a, int grid_wgs,
                         hipStream_t s);
-hipError_t launch_solve_mixed(int precision, int threads, const SolveArgs &a, int grid_wgs,
-                              hipStream_t s);
 hipError_t launch_class_order(const int *grid_id, int n, int n_grids, const RankTable &rank,
                               int *order, hipStream_t s);
 // Largest-first queue order of a single-class launch from per-item cost
@@ -106,8 +112,6 @@ hipError_t launch_cost_order(int n, const int *need, const int *cost, int *order
 hipError_t launch_note_cost(int n, const int *need, const int *iters, int *cost, hipStream_t s);
 bool mixed_supported(int n, int precision, int threads);
 bool tile_coop(int n, int precision, int cpt);  // a group of workgroups per item
-size_t mixed_slot_bytes(int n, int precision, int threads);
-int mixed_wgs_per_cu(int precision, int threads);
 bool tile_supported(int n, int precision, int cpt);
 bool tile_streamed(int n, int precision, int cpt);
 int solve_wgs_per_cu(int n, int precision, int cpt);

@@ -72,12 +72,13 @@ using S32 = Shape<32, 2, 8, 1>;
 using S64 = Shape<64, 4, 16, 1>;
 using S128 = Shape<128, 8, 16, 1>;
 
-// Reduction slots (FP64, W each): the predictor's 8 sums, then |r|^2, r.z,
-// p.q and the misfit or step size.  No two consecutive reductions share one.
+// Reduction slots (FP64, W each): the predictor's 8 sums of each species,
+// then |r|^2, r.z, p.q, the step size or true residual, and the misfit.  No
+// two consecutive reductions share one.
 template <int W>
 struct RedSlots {
-    static constexpr int gram = 0, rr = 8 * W, rz = 9 * W, pq = 10 * W, misc = 11 * W,
-                         total = 12 * W;
+    static constexpr int gram = 0, rr = 16 * W, rz = 17 * W, pq = 18 * W, misc = 19 * W,
+                         misfit = 20 * W, total = 21 * W;
 };
 
 // LDS of a workgroup.  qf / qt: Q and Q^T as matrix-core fragments (tile of
@@ -207,15 +208,19 @@ __device__ __forceinline__ double swap_add16(double a, double b)
            __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
 }
 
-// Workgroup sums of M values through slot[M][W]; every wave gets them in the
-// same order of additions.
+// The wave's totals of M values into slot[M][W].
 template <int W, int M>
-__device__ __forceinline__ void group_sum(double (&v)[M], double *slot, int w)
+__device__ __forceinline__ void wave_totals(const double (&v)[M], double *slot, int w)
 {
+    const int lane = lane_here(), row = lane >> 4;
     if constexpr (M < 3) {
-        block_sum_n<W>(v, slot, w);
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const double t = wave_sum_last_lane(v[m]);
+            if (lane == kLastLane)
+                slot[m * W + w] = t;
+        }
     } else {
-        const int lane = lane_here(), row = lane >> 4;
         const int m = row == 1 ? 2 : row == 2 ? 1 : row;
 #pragma unroll
         for (int m0 = 0; m0 < M; m0 += 4) {
@@ -229,9 +234,17 @@ __device__ __forceinline__ void group_sum(double (&v)[M], double *slot, int w)
             if ((lane & 15) == 15 && m0 + m < M)
                 slot[(m0 + m) * W + w] = t;
         }
-        __syncthreads();
-        slots_sum<W>(v, slot);
     }
+}
+
+// Workgroup sums of M values; every wave gets them in the same order of
+// additions.
+template <int W, int M>
+__device__ __forceinline__ void group_sum(double (&v)[M], double *slot, int w)
+{
+    wave_totals<W>(v, slot, w);
+    __syncthreads();
+    slots_sum<W>(v, slot);
 }
 
 // Q[k][i] = nrm cos(pi k (2 i + 1) / 2N), row 0 scaled by 1/sqrt(2); the
@@ -318,6 +331,7 @@ __device__ __forceinline__ void product(const _Float16 *m, const half8 (&a)[S::K
 // What a thread knows of its place and its item's arrays.
 template <class S>
 struct Ctx {
+    using Sh = S;
     Lds<S> &s;
     double *xs;       // fields (slot)
     float *hs;        // increments [species][buffer]
@@ -527,11 +541,13 @@ struct System {
 // step that it belongs to is solved; u of level n is read here for the last
 // time in the v system, v is first read at its new level in the next u
 // system): it is advanced on the way, and d recorded in increment buffer hb.
-template <class S, int kSp, bool kAdvance>
-__device__ __forceinline__ void residual(const Ctx<S> &x, const System &y, int fo, int ft,
-                                         float (&r)[S::R], float (&sg)[S::R], double &bb,
-                                         double &rr, double &es, const float (&d)[S::R], int hb)
+template <int kSp, bool kAdvance, class X>
+__device__ __forceinline__ void residual(const X &x, const System &y, int fo, int ft,
+                                         float (&r)[X::Sh::R], float (&sg)[X::Sh::R], double &bb,
+                                         double &rr, double &es, const float (&d)[X::Sh::R],
+                                         int hb)
 {
+    using S = typename X::Sh;
     constexpr int C = S::C, N = S::N, K = S::K, R = S::R;
     const double *own = x.field(fo) + x.row(0);
     double *oth = x.field(ft) + x.row(0);
@@ -628,9 +644,10 @@ __device__ __forceinline__ void residual(const Ctx<S> &x, const System &y, int f
 }
 
 // Own cells of a slot array.
-template <class S>
-__device__ __forceinline__ void load_strip(const Ctx<S> &x, const float *a, float (&v)[S::R])
+template <class X>
+__device__ __forceinline__ void load_strip(const X &x, const float *a, float (&v)[X::Sh::R])
 {
+    using S = typename X::Sh;
     const float *row = a + x.row(0);
     const unsigned o = opaque(x.o);
 #pragma unroll
@@ -654,11 +671,12 @@ struct Scalars {
 // of least energy-norm error over their span.  r becomes the residual of d0.
 // On entry bb, rr hold this thread's sums and es its sum of e; on return v
 // holds the item's.  `quiet`: r0 itself met the tolerance.
-template <class S>
-__device__ __forceinline__ void start(Ctx<S> &x, const System &y, int sp, int kn, int npred,
-                                      float (&r)[S::R], const float (&sg)[S::R], float (&d)[S::R],
-                                      double es, Scalars &v, int &quiet)
+template <class X>
+__device__ __forceinline__ void start(X &x, const System &y, int sp, int kn, int npred,
+                                      float (&r)[X::Sh::R], const float (&sg)[X::Sh::R],
+                                      float (&d)[X::Sh::R], double es, Scalars &v, int &quiet)
 {
+    using S = typename X::Sh;
     using RS = RedSlots<S::W>;
     constexpr int C = S::C, R = S::R, K = S::K, N = S::N;
     const float cf = uniform((float)y.c);
@@ -698,7 +716,7 @@ __device__ __forceinline__ void start(Ctx<S> &x, const System &y, int sp, int kn
             RD_PIN(g22);
         });
         double v8[8] = {v.bb, v.rr, es, g11, g12, g22, b1, b2};
-        x.sum(v8, RS::gram);
+        x.sum(v8, RS::gram + 8 * sp * S::W);
         v.bb = v8[0];
         v.rr = v8[1];
         es = v8[2];
@@ -745,7 +763,7 @@ __device__ __forceinline__ void start(Ctx<S> &x, const System &y, int sp, int kn
         }
     } else {
         double v3[3] = {v.bb, v.rr, es};
-        x.sum(v3, RS::gram);
+        x.sum(v3, RS::gram + 8 * sp * S::W);
         v.bb = v3[0];
         v.rr = v3[1];
         es = v3[2];
@@ -769,11 +787,12 @@ constexpr int kPlainCap = 16;
 
 // Preconditioned CG: d += A^-1 r until |r|^2 <= stop2 (r is updated
 // recursively).  Returns RD status bits.
-template <class S>
-__device__ __forceinline__ int pcg(Ctx<S> &x, const System &y, float (&r)[S::R],
-                                   const float (&sg)[S::R], float (&d)[S::R], double stop2,
-                                   Scalars &v)
+template <class X>
+__device__ __forceinline__ int pcg(X &x, const System &y, float (&r)[X::Sh::R],
+                                   const float (&sg)[X::Sh::R], float (&d)[X::Sh::R],
+                                   double stop2, Scalars &v)
 {
+    using S = typename X::Sh;
     using RS = RedSlots<S::W>;
     constexpr int C = S::C, R = S::R, N = S::N;
     const float cf = uniform((float)y.c);
@@ -876,15 +895,18 @@ __device__ __forceinline__ int pcg(Ctx<S> &x, const System &y, float (&r)[S::R],
         if (!finite(v.rr))
             st = kStNonfinite;
     }
+    if (x.failed())
+        st = kStGroupTimeout;
     return st;
 }
 
 // FP64 problems.  Adds the correction d to the new field fn (kFirst: to the
 // level-n field fo) and to the increment in buffer hb.
-template <class S>
-__device__ __forceinline__ void correct(const Ctx<S> &x, int sp, int fo, int fn, bool first,
-                                        const float (&d)[S::R], int hb)
+template <class X>
+__device__ __forceinline__ void correct(const X &x, int sp, int fo, int fn, bool first,
+                                        const float (&d)[X::Sh::R], int hb)
 {
+    using S = typename X::Sh;
     constexpr int C = S::C, N = S::N;
     const double *from = x.field(first ? fo : fn) + x.row(0);
     double *to = x.field(fn) + x.row(0);
@@ -921,10 +943,11 @@ __device__ __forceinline__ void correct(const Ctx<S> &x, int sp, int fo, int fn,
 // FP64 problems: residual of the implicit system for the new field,
 // r = src + (x - x') / dt - e x' - c t(x'), e from the level-n fields, and
 // this thread's sum of r^2.
-template <class S>
-__device__ __forceinline__ double true_residual(const Ctx<S> &x, const System &y, int sp, int fo,
-                                                int ft, int fn, float (&r)[S::R])
+template <class X>
+__device__ __forceinline__ double true_residual(const X &x, const System &y, int sp, int fo, int ft,
+                                                int fn, float (&r)[X::Sh::R])
 {
+    using S = typename X::Sh;
     constexpr int C = S::C, N = S::N, K = S::K;
     const double *nw = x.field(fn) + x.row(0), *own = x.field(fo) + x.row(0),
                  *oth = x.field(ft) + x.row(0);
@@ -987,11 +1010,12 @@ __device__ __forceinline__ double fp64_rtol2(double rtol2, const System &y)
 // evaluated residual meets the tolerance.  A residual that has stopped
 // falling although every correction converged is at the rounding level of
 // its own evaluation and is accepted.
-template <class S>
-__device__ __forceinline__ int refine(Ctx<S> &x, const System &y, int sp, int fo, int ft, int fn,
-                                      float (&r)[S::R], const float (&sg)[S::R], float (&d)[S::R],
-                                      Scalars &v, int hb)
+template <class X>
+__device__ __forceinline__ int refine(X &x, const System &y, int sp, int fo, int ft, int fn,
+                                      float (&r)[X::Sh::R], const float (&sg)[X::Sh::R],
+                                      float (&d)[X::Sh::R], Scalars &v, int hb)
 {
+    using S = typename X::Sh;
     bool first = true;
     double best = __builtin_inf();
     int stalled = 0;
@@ -1020,9 +1044,10 @@ __device__ __forceinline__ int refine(Ctx<S> &x, const System &y, int sp, int fo
 }
 
 // One item: all IMEX steps, then the outputs and the misfit.
-template <class S, bool kFp64>
-__device__ __forceinline__ void solve_item(const SolveArgs &a, int c, const GridDev &gd, Ctx<S> &x)
+template <bool kFp64, class X>
+__device__ __forceinline__ void solve_item(const SolveArgs &a, int c, const GridDev &gd, X &x)
 {
+    using S = typename X::Sh;
     constexpr int C = S::C, R = S::R, N = S::N, K = S::K;
     constexpr size_t NN = (size_t)N * N;
     const double th0 = a.theta[4 * c], th1 = a.theta[4 * c + 1], th2 = a.theta[4 * c + 2],
@@ -1074,9 +1099,9 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int c, const Grid
             double es;
             // (FP32: d is the increment of the other species' last system)
             if (sp == 0)
-                residual<S, 0, !kFp64>(x, y, fo, ft, r, sg, v.bb, v.rr, es, d, kn ^ 1);
+                residual<0, !kFp64>(x, y, fo, ft, r, sg, v.bb, v.rr, es, d, kn ^ 1);
             else
-                residual<S, 1, !kFp64>(x, y, fo, ft, r, sg, v.bb, v.rr, es, d, kn);
+                residual<1, !kFp64>(x, y, fo, ft, r, sg, v.bb, v.rr, es, d, kn);
             int still = 0;
             v.it = 0;
             v.maxit = a.maxit;
@@ -1168,7 +1193,7 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int c, const Grid
         group_end();
     }
     if (a.phi) {
-        sum = x.sum1(sum, RedSlots<S::W>::gram);
+        sum = x.sum1(sum, RedSlots<S::W>::misfit);
         if (x.leader())
             a.phi[c] = (st != 0 || !gd.y || !finite(sum)) ? __builtin_inf() : sum * gd.inv_2s2;
     }
@@ -1196,21 +1221,29 @@ constexpr size_t slot_bytes(bool fp64)
     return (size_t)S::cells * ((fp64 ? 4 : 2) * sizeof(double) + 4 * sizeof(float));
 }
 
+// Queue loop of a workgroup over the items of S's grid size (a launch over
+// several classes takes one kernel per size, each with a queue of its own).
+template <class S, bool kFp64>
+__device__ __forceinline__ void serve(const SolveArgs &a, Lds<S> &s, int *s_item)
+{
+    init_tables<S>(s);
+    Ctx<S> x(s, (char *)a.gws + (size_t)blockIdx.x * a.gws_stride, n_fields<kFp64>());
+    for (int item = next_item(a.queue, s_item); item < a.n_items;
+         item = next_item(a.queue, s_item)) {
+        const int c = uniform(a.order ? a.order[item] : item);
+        if (!a.need || uniform(a.need[c])) {
+            const int gid = item_grid(a, c);
+            if (gid >= 0 && uniform(a.grids[gid].n) == S::N)
+                solve_item<kFp64>(a, c, a.grids[gid], x);
+        }
+    }
+}
+
 template <class S, bool kFp64, int kWavesPerSimd>
 __global__ __launch_bounds__(S::T, kWavesPerSimd) void k_solve_pcg(SolveArgs a)
 {
     __shared__ __attribute__((aligned(16))) Lds<S> s;
-    init_tables<S>(s);
-    Ctx<S> x(s, (char *)a.gws + (size_t)blockIdx.x * a.gws_stride, n_fields<kFp64>());
-    for (int item = next_item(a.queue, &s.item); item < a.n_items;
-         item = next_item(a.queue, &s.item)) {
-        const int c = uniform(a.order ? a.order[item] : item);
-        if (!a.need || uniform(a.need[c])) {
-            const int gid = item_grid(a, c);
-            if (gid >= 0)
-                solve_item<S, kFp64>(a, c, a.grids[gid], x);
-        }
-    }
+    serve<S, kFp64>(a, s, &s.item);
 }
 
 }  // namespace pcg

@@ -1120,7 +1120,7 @@ __global__ __launch_bounds__(N *N / R) void k_solve_resident(SolveArgs a)
         const int c = uniform(a.order ? a.order[item] : item);
         if (!a.need || uniform(a.need[c])) {
             const int gid = item_grid(a, c);
-            if (gid >= 0)
+            if (gid >= 0 && uniform(a.grids[gid].n) == N)
                 solve_item_resident<N, R, Real, true>(a, c, a.grids[gid], P, stash, red, slot);
         }
     }
@@ -1149,31 +1149,6 @@ __global__ __launch_bounds__(N *N / R) void k_solve_streamed(SolveArgs a)
 #include "rd_pcg.hpp"
 
 namespace rd {
-
-// Uneven batches: one persistent launch of T-thread workgroups serves items
-// of every grid class.  Each class runs the strip layout that T threads give
-// it (R = n^2 / T cells per thread): resident where its arrays fit the VGPR
-// and LDS budget, streamed otherwise.  The queue is ordered by decreasing
-// cost (a.order), so that the large solves start first and the small ones
-// fill the tail.
-template <typename Real>
-struct MixedTraits {
-    static constexpr int kMaxResident = sizeof(Real) == 4 ? 128 : 64;
-};
-
-template <int N, int T, typename Real>
-__device__ __forceinline__ void solve_item_class(const SolveArgs &a, int c, const GridDev &gd,
-                                                 Real *P, Real *stash, double *red, Real *slot)
-{
-    if constexpr (N * N >= T) {
-        constexpr int R = N * N / T;
-        if constexpr (N <= MixedTraits<Real>::kMaxResident && R <= 32 / (sizeof(Real) / 4))
-            solve_item_resident<N, R, Real>(a, c, gd, P, stash, red, slot);
-        else
-            solve_item_streamed<N, R, Real>(a, c, gd, red, slot);
-    }
-}
-
 
 // Queue order of a mixed batch: the stable counting sort of the items by
 // grid class in the order `rank` (rank[g] = position of class g, most costly
@@ -2026,8 +2001,8 @@ __device__ void solve_item_coop(const SolveArgs &a, int c, const GridDev &gd, fl
 }
 
 // Marks queue items failed, starting with the one in *s_item, until the
-// queue (or, with prefix_only, its 256^2 prefix) is exhausted.
-__device__ void coop_drain(const SolveArgs &a, bool prefix_only, unsigned *queue, int *s_item)
+// queue is exhausted.
+__device__ void coop_drain(const SolveArgs &a, unsigned *queue, int *s_item)
 {
     int item = uniform(*s_item);
     __syncthreads();
@@ -2035,8 +2010,6 @@ __device__ void coop_drain(const SolveArgs &a, bool prefix_only, unsigned *queue
         const int c = uniform(a.order ? a.order[item] : item);
         const int gid = uniform(a.grid_id ? a.grid_id[c] : 0);
         const bool bad = (unsigned)gid >= (unsigned)a.n_grids;
-        if (prefix_only && (bad || uniform(a.grids[gid].n) != kCoopN))
-            break;
         if (threadIdx.x == 0 && (!a.need || a.need[c])) {
             a.status[c] = bad ? kStBadGrid : kStGroupTimeout;
             if (a.phi)
@@ -2058,11 +2031,8 @@ __device__ void coop_drain(const SolveArgs &a, bool prefix_only, unsigned *queue
 
 // Groups pull items from a queue of their own (the first word of the
 // workspace): member 0 takes the next index and the group exchange hands it
-// to the other members.  With `prefix_only` the queue is class-ordered and
-// the 256^2 items form its prefix: a group stops at the first item of
-// another class (or with an invalid class, which sorts last); a following
-// launch serves the rest.
-__device__ __forceinline__ void coop_run(const SolveArgs &a, bool prefix_only, float *P, float *stash,
+// to the other members.
+__device__ __forceinline__ void coop_run(const SolveArgs &a, float *P, float *stash,
                          double *red, double *gather, int *fail, int *s_item)
 {
     // group of this workgroup: ids congruent modulo 8 share an XCD
@@ -2101,7 +2071,7 @@ __device__ __forceinline__ void coop_run(const SolveArgs &a, bool prefix_only, f
             // resident): the group stops exchanging, and member 0 marks
             // the items it still pulls, its last one included, as failed.
             if (member == 0)
-                coop_drain(a, prefix_only, queue, s_item);
+                coop_drain(a, queue, s_item);
             break;
         }
         const int item = (int)(v[0] + 0.5);
@@ -2110,8 +2080,6 @@ __device__ __forceinline__ void coop_run(const SolveArgs &a, bool prefix_only, f
         const int c = uniform(a.order ? a.order[item] : item);
         const int gid = uniform(a.grid_id ? a.grid_id[c] : 0);
         const bool bad = (unsigned)gid >= (unsigned)a.n_grids;
-        if (prefix_only && (bad || uniform(a.grids[gid].n) != kCoopN))
-            break;
         if (a.need && !uniform(a.need[c]))
             continue;
         if (bad) {
@@ -2145,82 +2113,20 @@ __global__ __launch_bounds__(kCoopThreads) void k_solve_coop(SolveArgs a)
     __shared__ double gather[kCoopG * 4];
     __shared__ int fail;
     __shared__ int s_item;
-    coop_run(a, a.coop_wgs > 0, P, stash, red, gather, &fail, &s_item);
+    coop_run(a, P, stash, red, gather, &fail, &s_item);
 }
 
 
-template <int T, typename Real>
-__global__ __launch_bounds__(T) void k_solve_mixed(SolveArgs a)
-{
-    constexpr int NW = T / kWave;
-    constexpr int NM = MixedTraits<Real>::kMaxResident;
-    __shared__ Real P[NM * NM];
-    __shared__ Real stash[NM * NM];
-    __shared__ double red[Slots<NW>::total];
-    __shared__ int s_item;
-    Real *slot = (Real *)((char *)a.gws + (size_t)blockIdx.x * a.gws_stride);
-    for (int item = next_item(a.queue, &s_item); item < a.n_items;
-         item = next_item(a.queue, &s_item)) {
-        const int c = uniform(a.order ? a.order[item] : item);
-        const int gid = (!a.need || uniform(a.need[c])) ? item_grid(a, c) : -1;
-        if (gid >= 0) {
-            const GridDev &gd = a.grids[gid];
-            const int n = uniform(gd.n);
-            if (n == 32)
-                solve_item_class<32, T, Real>(a, c, gd, P, stash, red, slot);
-            else if (n == 64)
-                solve_item_class<64, T, Real>(a, c, gd, P, stash, red, slot);
-            else if (n == 128)
-                solve_item_class<128, T, Real>(a, c, gd, P, stash, red, slot);
-            else if (n == 256 && !a.coop_wgs)  // else the cooperative launch solved it
-                solve_item_class<256, T, Real>(a, c, gd, P, stash, red, slot);
-        }
-    }
-}
+}  // namespace rd
 
+#include "rd_pcg_group.hpp"
 
-// Mixed launch with the cooperative role (FP32, 1024 threads): the first
-// a.coop_wgs workgroups (a multiple of 32, all resident: they have the
-// lowest ids, so they are dispatched first) serve the 256^2 prefix of the
-// class-ordered queue in groups of four, then join the queue of the other
-// classes, which the remaining workgroups serve from the start.  Classes
-// 32^2 .. 128^2 run resident.
-__global__ __launch_bounds__(kCoopThreads) void k_solve_mixed_coop(SolveArgs a)
-{
-    constexpr int T = kCoopThreads, NW = T / kWave, NM = 128;
-    constexpr int kP = (kCoopStrip + 2) * kCoopN;
-    static_assert(kP >= NM * NM, "LDS P holds a 128^2 item");
-    __shared__ float P[kP];
-    __shared__ float stash[NM * NM];
-    __shared__ double red[Slots<NW>::total];
-    __shared__ double gather[kCoopG * 4];
-    __shared__ int fail;
-    __shared__ int s_item;
-    if ((int)blockIdx.x < a.coop_wgs)
-        coop_run(a, true, P, stash, red, gather, &fail, &s_item);
-    float *slot = (float *)((char *)a.gws + (size_t)blockIdx.x * a.gws_stride);
-    for (int item = next_item(a.queue, &s_item); item < a.n_items;
-         item = next_item(a.queue, &s_item)) {
-        const int c = uniform(a.order ? a.order[item] : item);
-        const int gid = (!a.need || uniform(a.need[c])) ? item_grid(a, c) : -1;
-        if (gid >= 0) {
-            const GridDev &gd = a.grids[gid];
-            const int n = uniform(gd.n);
-            if (n == 32)
-                solve_item_class<32, T, float>(a, c, gd, P, stash, red, slot);
-            else if (n == 64)
-                solve_item_class<64, T, float>(a, c, gd, P, stash, red, slot);
-            else if (n == 128)
-                solve_item_class<128, T, float>(a, c, gd, P, stash, red, slot);
-        }
-    }
-}
+namespace rd {
 
 // wgs: the most workgroups that are resident at once (every member of a
 // group must be, since members wait for each other).  The launch uses whole
 // blocks of 32 workgroups (8 groups, one per XCD) and no more groups than
-// items.  a.coop_wgs > 0 marks a class-ordered batch whose 256^2 prefix
-// this launch serves (the mixed launch that follows serves the rest).
+// items.
 hipError_t launch_solve_coop(const SolveArgs &a, int wgs, hipStream_t s)
 {
     const int need = (a.n_items * kCoopG + 31) / 32 * 32;
@@ -2276,10 +2182,12 @@ hipError_t launch_fill_u32(unsigned *p, unsigned v, int count, hipStream_t s)
 // fit the VGPR budget of the workgroup size.
 namespace {
 
-enum Kind { kNone, kResident, kStreamed, kCoop, kSpectral };
+enum Kind { kNone, kResident, kStreamed, kCoop, kSpectral, kSpectralGroup };
 
 Kind tile_kind(int n, int precision, int cpt)
 {
+    if (n == 256 && cpt == kGroupCpt)
+        return kSpectralGroup;
     if (precision == 0) {
         // one kernel serves every tile of these sizes
         if ((n == 32 && (cpt == 4 || cpt == 8 || cpt == 16)) ||
@@ -2345,20 +2253,21 @@ bool tile_supported(int n, int precision, int cpt)
 // first 500 steps, 42.8 against 89.5 ms; 4096 prior draws, first 200 steps, 150
 // against 625 ms (51 CG iterations per step against 3); one item 36 against 111 us
 // per step; 2000 prior draws of 64^2 25.7 against 68 ms; 5000 growing items of
-// 32^2 15.0 against 20.4 ms; 64 items of 128^2 in FP64 4.3 against 144 ms.  At 256^2 in FP32 the cooperative
-// tile (16 cells per thread, four workgroups per item) is 9 to 14 times
-// faster per item than the streamed one.
+// 32^2 15.0 against 20.4 ms; 64 items of 128^2 in FP64 4.3 against 144 ms; 37
+// items of 256^2 by groups of four workgroups 6.6 against 41.6 ms.
 int default_cpt(int n, int precision)
 {
     if (precision == 0)
-        return n == 32 ? 16 : n == 64 ? 16 : n == 128 ? 32 : n == 256 ? kCoopR : 0;
-    return n == 32 ? 8 : n == 64 ? 16 : n == 128 ? 32 : n == 256 ? 128 : 0;
+        return n == 32 ? 16 : n == 64 ? 16 : n == 128 ? 32 : n == 256 ? kGroupCpt : 0;
+    return n == 32 ? 8 : n == 64 ? 16 : n == 128 ? 32 : n == 256 ? kGroupCpt : 0;
 }
 
 size_t solve_slot_bytes(int n, int precision, int cpt)
 {
     if (tile_kind(n, precision, cpt) == kCoop)  // one member's strip: 4 arrays
         return (size_t)4 * kCoopStrip * kCoopN * sizeof(float);
+    if (tile_kind(n, precision, cpt) == kSpectralGroup)
+        return pcg::slot_bytes<pcg::S256>(precision != 0);
     if (tile_kind(n, precision, cpt) == kSpectral)
         return n == 32   ? pcg::slot_bytes<pcg::S32>(precision != 0)
                : n == 64 ? pcg::slot_bytes<pcg::S64>(precision != 0)
@@ -2388,6 +2297,9 @@ int solve_wgs_per_cu(int n, int precision, int cpt)
         return occupancy(k_solve_streamed<NN, RR, T>, NN * NN / RR);
     if (tile_kind(n, precision, cpt) == kCoop)
         return occupancy(k_solve_coop, kCoopThreads);
+    if (tile_kind(n, precision, cpt) == kSpectralGroup)
+        return precision ? occupancy(pcg::k_solve_group<true>, pcg::S256::T)
+                         : occupancy(pcg::k_solve_group<false>, pcg::S256::T);
     if (tile_kind(n, precision, cpt) == kSpectral) {
         int wgs = 1;
         spectral(n, precision, [&](auto kernel, int threads) { wgs = occupancy(kernel, threads); });
@@ -2404,32 +2316,10 @@ int solve_wgs_per_cu(int n, int precision, int cpt)
     return 1;
 }
 
-// Mixed launch: T threads per workgroup for every class.
-static bool mixed_resident(int n, int precision, int threads)
-{
-    const int r = n * n / threads;
-    return n <= (precision ? 64 : 128) && r <= (precision ? 16 : 32);
-}
-
 bool mixed_supported(int n, int precision, int threads)
 {
     return (threads == 512 || threads == 1024) && (n == 32 || n == 64 || n == 128 || n == 256) &&
            n * n >= threads;
-}
-
-size_t mixed_slot_bytes(int n, int precision, int threads)
-{
-    const size_t arrays = mixed_resident(n, precision, threads) ? 6 : 12;
-    return arrays * n * n * (precision ? sizeof(double) : sizeof(float));
-}
-
-int mixed_wgs_per_cu(int precision, int threads)
-{
-    if (precision == 0)
-        return threads == 512 ? occupancy(k_solve_mixed<512, float>, 512)
-                              : occupancy(k_solve_mixed<1024, float>, 1024);
-    return threads == 512 ? occupancy(k_solve_mixed<512, double>, 512)
-                          : occupancy(k_solve_mixed<1024, double>, 1024);
 }
 
 hipError_t launch_cost_order(int n, const int *need, const int *cost, int *order, hipStream_t s)
@@ -2455,45 +2345,62 @@ hipError_t launch_class_order(const int *grid_id, int n, int n_grids, const Rank
     return hipGetLastError();
 }
 
-hipError_t launch_solve_mixed(int precision, int threads, const SolveArgs &a, int wgs,
-                              hipStream_t s)
+size_t group_workspace_bytes(int groups)
 {
-    if (!a.gws || wgs > a.gws_slots || !a.order)
-        return hipErrorInvalidValue;
-    if (precision == 0) {
-        if (threads == 512)
-            hipLaunchKernelGGL((k_solve_mixed<512, float>), dim3(wgs), dim3(512), 0, s, a);
-        else
-            hipLaunchKernelGGL((k_solve_mixed<1024, float>), dim3(wgs), dim3(1024), 0, s, a);
-    } else {
-        if (threads == 512)
-            hipLaunchKernelGGL((k_solve_mixed<512, double>), dim3(wgs), dim3(512), 0, s, a);
-        else
-            hipLaunchKernelGGL((k_solve_mixed<1024, double>), dim3(wgs), dim3(1024), 0, s, a);
-    }
+    return pcg::GroupArea::bytes(groups);
+}
+
+hipError_t launch_group_tables(void *ws, int groups, hipStream_t s)
+{
+    using namespace pcg;
+    _Float16 *t = (_Float16 *)((char *)ws + GroupArea::head(groups));
+    constexpr int kEntries = S256::N * S256::N;
+    hipLaunchKernelGGL(k_group_tables, dim3(kEntries / 256), dim3(256), 0, s, t, t + kEntries);
     return hipGetLastError();
 }
 
-int mixed_coop_wgs_per_cu()
+// 256^2 items (and, mixed, then the 128^2 items of a class-ordered batch) on
+// wgs workgroups that are all resident; the first a.coop_wgs of them, whole
+// blocks of 32, form the groups.
+hipError_t launch_solve_group(int precision, SolveArgs a, int wgs, bool mixed, hipStream_t s)
 {
-    return occupancy(k_solve_mixed_coop, kCoopThreads);
+    using namespace pcg;
+    if (!mixed) {
+        const int need = (a.n_items * S256::G + 31) / 32 * 32;
+        wgs = a.coop_wgs = std::min(wgs / 32 * 32, need);
+    }
+    if (!a.gws || wgs < 1 || wgs > a.gws_slots || a.coop_wgs > wgs || a.coop_wgs % 32 != 0 ||
+        (!mixed && a.coop_wgs < 32) || (mixed && !a.order) ||
+        a.gws_stride < slot_bytes<S256>(precision != 0))
+        return hipErrorInvalidValue;
+    if (a.coop_wgs > 0) {
+        if (!a.group_ws || a.coop_wgs / S256::G > a.group_cap)
+            return hipErrorInvalidValue;
+        // the queue starts at 0, and stale tags of an earlier launch must not
+        // match this launch's
+        const size_t head = GroupArea::head(a.coop_wgs / S256::G);
+        const hipError_t e = launch_fill_u32((unsigned *)a.group_ws, 0u, (int)(head / 4), s);
+        if (e != hipSuccess)
+            return e;
+    }
+    if (precision)
+        hipLaunchKernelGGL(k_solve_group<true>, dim3(wgs), dim3(S256::T), 0, s, a, mixed);
+    else
+        hipLaunchKernelGGL(k_solve_group<false>, dim3(wgs), dim3(S256::T), 0, s, a, mixed);
+    return hipGetLastError();
 }
 
-// Mixed batch with 256^2 FP32 items and 1024-thread workgroups: one launch
-// of k_solve_mixed_coop (a.coop_wgs leading workgroups in the cooperative
-// role).  The caller has class-ordered the queue (a.order).
-hipError_t launch_solve_mixed_coop(const SolveArgs &a, int wgs, hipStream_t s)
+// The items of one small class size (32 or 64) of a class-ordered batch.
+hipError_t launch_solve_class(int n, int precision, const SolveArgs &a, int wgs, hipStream_t s)
 {
-    if (!a.gws || !a.order || !a.coop || wgs > a.gws_slots || a.coop_wgs < 32 ||
-        a.coop_wgs % 32 != 0 || a.coop_wgs > wgs || a.coop_wgs / kCoopG > a.coop_groups ||
-        a.gws_stride < (size_t)4 * kCoopStrip * kCoopN * sizeof(float))
+    if (!a.gws || !a.order || wgs < 1 || wgs > a.gws_slots || (n != 32 && n != 64) ||
+        a.gws_stride < solve_slot_bytes(n, precision, default_cpt(n, precision)))
         return hipErrorInvalidValue;
-    hipError_t e = launch_fill_u32((unsigned *)a.coop, 0u,
-                                   (int)(coop_workspace_bytes(a.coop_wgs / kCoopG) / sizeof(unsigned)),
-                                   s);
-    if (e != hipSuccess)
-        return e;
-    hipLaunchKernelGGL(k_solve_mixed_coop, dim3(wgs), dim3(kCoopThreads), 0, s, a);
+    if (n == 32 && precision)
+        return go_resident<32, 8, double>(a, wgs, s);
+    spectral(n, precision, [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(wgs), dim3(threads), 0, s, a);
+    });
     return hipGetLastError();
 }
 
@@ -2504,7 +2411,8 @@ bool tile_streamed(int n, int precision, int cpt)
 
 bool tile_coop(int n, int precision, int cpt)
 {
-    return tile_kind(n, precision, cpt) == kCoop;
+    const Kind k = tile_kind(n, precision, cpt);
+    return k == kCoop || k == kSpectralGroup;
 }
 
 hipError_t launch_solve(int n, int precision, TileChoice tile, const SolveArgs &a, int wgs,
@@ -2523,6 +2431,8 @@ hipError_t launch_solve(int n, int precision, TileChoice tile, const SolveArgs &
         return go_streamed<NN, RR, T>(a, wgs, s);
     if (tile_kind(n, precision, cpt) == kCoop)
         return launch_solve_coop(a, wgs, s);
+    if (tile_kind(n, precision, cpt) == kSpectralGroup)
+        return launch_solve_group(precision, a, wgs, false, s);
     if (tile_kind(n, precision, cpt) == kSpectral) {
         spectral(n, precision, [&](auto kernel, int threads) {
             hipLaunchKernelGGL(kernel, dim3(wgs), dim3(threads), 0, s, a);
