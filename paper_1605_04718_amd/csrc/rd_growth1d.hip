@@ -2,19 +2,23 @@
 // IMEX solves with a growth function rho(t), the misfit at T, and the C ABI
 // of include/rdbayes_growth1d.h.
 //
-// One wavefront per item.  Lane L owns rows L and L + 64 of both tridiagonal
-// systems (u and v), so n <= 128 cells fit one wave; rows past n are
-// identity rows (a = c = 0, b = 1, d = 0) that no real row couples to.
-// Parallel cyclic reduction: at stride s every row eliminates its couplings
-// to rows i - s and i + s with those rows' equations, which leaves
-// couplings at stride 2s.  For n <= 64 the levels run until each row stands
-// alone (x_i = d_i / b_i); for n > 64 they stop after stride 32, where row i
-// couples only to i +- 64, so rows L and L + 64 form a 2 x 2 system inside
-// lane L and the last level needs no exchange.  Every row publishes
-// (a/b, c/b, d/b) once per level (one reciprocal per row and level) in LDS,
-// laid out [system][component][row] so that a wave's accesses are
-// consecutive.  The fields stay in registers
-// for the whole horizon; only the data and the results touch HBM.
+// Sixteen lanes per item, four items per wavefront.  Lane L of an item owns
+// the M = ceil(n / 16) neighbouring rows L M .. L M + M - 1 of both
+// tridiagonal systems (u and v), so n <= 128 cells fit; rows past n carry
+// zeros and no coupling.  Each lane eliminates inside its rows (forward, then
+// backward, which leaves its first row as a function of its own last row and
+// of the last row of the lane before), the sixteen last rows form a
+// tridiagonal system that four levels of parallel cyclic reduction solve with
+// lane shifts inside a 16-lane row, and the lane's other rows follow by
+// substitution: 20 operations per row and system plus 26 per level, where
+// cyclic reduction over all rows takes 16 per row, system and each of its six
+// levels and an LDS round trip with a barrier per level.  The fields stay in
+// registers for the whole horizon; only the data and the results touch HBM.
+//
+// What bounds it: FP64 issue, with one wavefront per SIMD at 4096 items.
+// Measured, n = 100, 1000 steps of 4096 items: 1.21 ms; cyclic reduction over
+// all rows by one wavefront per item 7.46 ms.
+
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -23,16 +27,17 @@
 #include <hip/hip_runtime.h>
 
 #include "../../include/rdbayes_growth1d.h"
+#include "rd_device.hpp"
 #include "rd_sampler.hpp"
 
 namespace rd {
 namespace g1d {
 
-constexpr int kRows = 128;  // rows per system, two per lane
+constexpr int kLanes = 16;  // lanes of an item (a DPP row)
 
 struct Args {
     int n, n_steps, law, obs;
-    double inv_tau, tau, T, rho_T;
+    double inv_tau, tau, inv_T, rho_T;
     double a, b, g, d;
     double inv_2s2;           // 1 / (2 sigma^2)
     const double *u0, *v0;    // [n]
@@ -52,9 +57,9 @@ __device__ inline void growth(const Args &a, double b1, double b2, double b3, do
                               double &rho, double &drho)
 {
     if (a.law == G1D_LAW_POLY) {
-        const double s = t / a.T;
+        const double s = t * a.inv_T;
         rho = 1.0 + s * (b1 + s * (b2 + s * (b3 + s * b4)));
-        drho = (b1 + s * (2.0 * b2 + s * (3.0 * b3 + s * 4.0 * b4))) / a.T;
+        drho = (b1 + s * (2.0 * b2 + s * (3.0 * b3 + s * 4.0 * b4))) * a.inv_T;
     } else if (a.law == G1D_LAW_EXP) {
         rho = exp(0.001 * t);
         drho = 0.001 * rho;
@@ -66,10 +71,6 @@ __device__ inline void growth(const Args &a, double b1, double b2, double b3, do
         drho = 0.01 * e * (1.0 - 1.0 / K) / (D * D);
     }
 }
-
-struct Row {
-    double A, B, C, D;
-};
 
 // 1/x from the hardware estimate refined by two Newton steps (e = 1 - x r,
 // r <- r + r e); each step squares the relative error, so the result is
@@ -84,169 +85,186 @@ __device__ inline double recip(double x)
     return fma(r, e, r);
 }
 
-// One reduction level at stride s for the four rows a lane owns.
-// P[sys][comp][row] holds (A/B, C/B, D/B) of every row of the level.
-__device__ inline void pcr_level(Row (&r)[2][2], double (*P)[3][kRows], int lane, int s)
+// The value of the lane kBy before (after) this one in its item, zero past
+// the item's ends.
+template <int kBy>
+__device__ __forceinline__ double before(double v)
 {
-#pragma unroll
-    for (int sys = 0; sys < 2; ++sys)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int i = lane + 64 * j;
-            const double rb = recip(r[sys][j].B);
-            P[sys][0][i] = r[sys][j].A * rb;
-            P[sys][1][i] = r[sys][j].C * rb;
-            P[sys][2][i] = r[sys][j].D * rb;
-        }
-    __syncthreads();
-    Row nr[2][2];
-#pragma unroll
-    for (int sys = 0; sys < 2; ++sys)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int i = lane + 64 * j;
-            double am = 0.0, cm = 0.0, dm = 0.0, ap = 0.0, cp = 0.0, dp = 0.0;
-            if (i - s >= 0) {
-                am = P[sys][0][i - s];
-                cm = P[sys][1][i - s];
-                dm = P[sys][2][i - s];
-            }
-            if (i + s < kRows) {
-                ap = P[sys][0][i + s];
-                cp = P[sys][1][i + s];
-                dp = P[sys][2][i + s];
-            }
-            const Row &q = r[sys][j];
-            nr[sys][j].A = -q.A * am;
-            nr[sys][j].C = -q.C * cp;
-            nr[sys][j].B = q.B - q.A * cm - q.C * ap;
-            nr[sys][j].D = q.D - q.A * dm - q.C * dp;
-        }
-    __syncthreads();  // every read of this level precedes the next level's writes
-#pragma unroll
-    for (int sys = 0; sys < 2; ++sys)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-            r[sys][j] = nr[sys][j];
+    return dpp_f64<0x110 + kBy, 0xF>(v);
+}
+template <int kBy>
+__device__ __forceinline__ double after(double v)
+{
+    return dpp_f64<0x100 + kBy, 0xF>(v);
 }
 
-__device__ inline double wave_sum(double x)
+// One level of cyclic reduction on the rows a x- + b x + c x+ = d of the two
+// systems, x-, x+ the unknowns kBy lanes away.
+template <int kBy>
+__device__ __forceinline__ void pcr_level(double (&a)[2], double (&b)[2], double (&c)[2],
+                                          double (&d)[2])
 {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-        x += __shfl_xor(x, o, 64);
+    for (int s = 0; s < 2; ++s) {
+        const double rb = recip(b[s]);
+        const double ar = a[s] * rb, cr = c[s] * rb, dr = d[s] * rb;
+        const double am = before<kBy>(ar), cm = before<kBy>(cr), dm = before<kBy>(dr);
+        const double ap = after<kBy>(ar), cp = after<kBy>(cr), dp = after<kBy>(dr);
+        b[s] = fma(-a[s], cm, fma(-c[s], ap, b[s]));
+        d[s] = fma(-a[s], dm, fma(-c[s], dp, d[s]));
+        a[s] = -a[s] * am;
+        c[s] = -c[s] * cp;
+    }
+}
+
+// Sum over the lanes of an item, in its last lane.
+__device__ __forceinline__ double item_sum(double x)
+{
+    x += before<1>(x);
+    x += before<2>(x);
+    x += before<4>(x);
+    x += before<8>(x);
     return x;
 }
 
+template <int M>
 __global__ __launch_bounds__(64) void k_g1d_solve(Args a)
 {
-    __shared__ double P[2][3][kRows];
-    const int lane = threadIdx.x;
-    const int item = blockIdx.x;
-    if (item >= a.m)
-        return;
-    const int n = a.n;
-    int st = 0;
-    double u[2], v[2];
+    const int lane = threadIdx.x & (kLanes - 1), sub = threadIdx.x / kLanes;
+    const int item = blockIdx.x * (64 / kLanes) + sub;
+    const int n = a.n, i0 = lane * M;
+    int st = item < a.m ? 0 : RD_ST_OUT_OF_PRIOR;
+    // x[0] = u, x[1] = v; cpl: 1 where row j couples to row j + 1; nb: number
+    // of neighbours; src: source terms (all zero in rows past n)
+    double x[2][M], cpl[M], nb[M], src[2][M];
+    const double left = lane > 0 && i0 < n ? 1.0 : 0.0;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int i = lane + 64 * j;
-        u[j] = i < n ? a.u0[i] : 0.0;
-        v[j] = i < n ? a.v0[i] : 0.0;
+    for (int j = 0; j < M; ++j) {
+        const int i = i0 + j;
+        const bool in = i < n;
+        x[0][j] = in ? a.u0[i] : 0.0;
+        x[1][j] = in ? a.v0[i] : 0.0;
+        cpl[j] = i + 1 < n ? 1.0 : 0.0;
+        nb[j] = cpl[j] + (in && i > 0 ? 1.0 : 0.0);
+        src[0][j] = in ? a.g * a.a : 0.0;
+        src[1][j] = in ? a.g * a.b : 0.0;
     }
     double b1 = 0.0, b2 = 0.0, b3 = 0.0, b4 = 0.0;
-    if (a.law == G1D_LAW_POLY) {
+    if (a.law == G1D_LAW_POLY && st == 0) {
         const double *bp = a.beta + (size_t)item * a.beta_stride;
         b1 = bp[0];
         b2 = bp[1];
         b3 = bp[2];
         b4 = a.rho_T - 1.0 - b1 - b2 - b3;
     }
-    if (a.need && !a.need[item])
+    if (st == 0 && a.need && !a.need[item])
         st = RD_ST_OUT_OF_PRIOR;
     const double nn = (double)n * (double)n;
-    for (int k = 0; k < a.n_steps && st == 0; ++k) {
-        double rho, drho;
-        growth(a, b1, b2, b3, b4, (double)k * a.tau, rho, drho);
-        if (!(rho > 0.0)) {
-            st = RD_ST_OUT_OF_PRIOR;  // uniform over the wave: rho depends on t only
-            break;
-        }
-        const double dil = drho / rho;
-        const double ku = nn / (rho * rho);
-        const double kv = a.d * ku;
-        Row r[2][2];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int i = lane + 64 * j;
-            if (i < n) {
-                const double nb = (i == 0 || i == n - 1) ? 1.0 : 2.0;
-                r[0][j].A = i > 0 ? -ku : 0.0;
-                r[0][j].C = i < n - 1 ? -ku : 0.0;
-                r[0][j].B = a.inv_tau + dil + a.g * (1.0 - u[j] * v[j]) + ku * nb;
-                r[0][j].D = u[j] * a.inv_tau + a.g * a.a;
-                r[1][j].A = i > 0 ? -kv : 0.0;
-                r[1][j].C = i < n - 1 ? -kv : 0.0;
-                r[1][j].B = a.inv_tau + dil + a.g * u[j] * u[j] + kv * nb;
-                r[1][j].D = v[j] * a.inv_tau + a.g * a.b;
+    for (int k = 0; k < a.n_steps && __any(st == 0); ++k) {
+        if (st == 0) {  // (all or none of an item's lanes)
+            double rho, drho;
+            growth(a, b1, b2, b3, b4, (double)k * a.tau, rho, drho);
+            if (!(rho > 0.0)) {
+                st = RD_ST_OUT_OF_PRIOR;
             } else {
-                r[0][j] = Row{0.0, 1.0, 0.0, 0.0};
-                r[1][j] = Row{0.0, 1.0, 0.0, 0.0};
-            }
-        }
-        const int s_end = n > 64 ? 64 : n;
-        for (int s = 1; s < s_end; s <<= 1)
-            pcr_level(r, P, lane, s);
-        if (n > 64) {
-            // rows p = lane and q = lane + 64: B_p x_p + C_p x_q = D_p,
-            // A_q x_p + B_q x_q = D_q (the outward couplings are zero)
-            double x[2][2];
+                const double rr = recip(rho);
+                const double base = fma(drho, rr, a.inv_tau);
+                double kk[2];
+                kk[0] = nn * rr * rr;
+                kk[1] = a.d * kk[0];
+                // rows after the forward pass: x_j = dr + fr x_left + cr x_{j+1}
+                double cr[2][M], dr[2][M], fr[2][M], c[2], b[2], d[2], f[2];
+                f[0] = kk[0] * left;
+                f[1] = kk[1] * left;
 #pragma unroll
-            for (int sys = 0; sys < 2; ++sys) {
-                const Row &p = r[sys][0], &q = r[sys][1];
-                const double inv = recip(p.B * q.B - p.C * q.A);
-                x[sys][0] = (p.D * q.B - p.C * q.D) * inv;
-                x[sys][1] = (p.B * q.D - q.A * p.D) * inv;
-            }
-            u[0] = x[0][0];
-            u[1] = x[0][1];
-            v[0] = x[1][0];
-            v[1] = x[1][1];
-        } else {
+                for (int j = 0; j < M; ++j) {
+                    const double gu = a.g * x[0][j];
+                    double bj[2], dj[2];
+                    bj[0] = fma(kk[0], nb[j], fma(-gu, x[1][j], base + a.g));
+                    bj[1] = fma(kk[1], nb[j], fma(gu, x[0][j], base));
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                u[j] = r[0][j].D * recip(r[0][j].B);
-                v[j] = r[1][j].D * recip(r[1][j].B);
+                    for (int s = 0; s < 2; ++s) {
+                        dj[s] = fma(x[s][j], a.inv_tau, src[s][j]);
+                        if (j > 0) {  // c: coupling of row j - 1 to this one
+                            bj[s] = fma(-c[s], cr[s][j - 1], bj[s]);
+                            dj[s] = fma(c[s], dr[s][j - 1], dj[s]);
+                            f[s] = c[s] * fr[s][j - 1];
+                        }
+                        c[s] = kk[s] * cpl[j];
+                        if (j < M - 1) {
+                            const double rb = recip(bj[s]);
+                            cr[s][j] = c[s] * rb;
+                            dr[s][j] = dj[s] * rb;
+                            fr[s][j] = f[s] * rb;
+                        }
+                        b[s] = bj[s];
+                        d[s] = dj[s];
+                    }
+                }
+                // the first row in terms of x_left and the last row:
+                // x_0 = A + B x_left + E x_last; the next lane's closes the
+                // equation of this lane's last row
+                double aa[2], cc[2];
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    double A = 0.0, B = 0.0, E = 1.0;
+#pragma unroll
+                    for (int j = M - 2; j >= 0; --j) {
+                        A = fma(cr[s][j], A, dr[s][j]);
+                        B = fma(cr[s][j], B, fr[s][j]);
+                        E = cr[s][j] * E;
+                    }
+                    const double An = after<1>(A), Bn = after<1>(B), En = after<1>(E);
+                    aa[s] = -f[s];
+                    b[s] = fma(-c[s], Bn, b[s]);
+                    cc[s] = -c[s] * En;
+                    d[s] = fma(c[s], An, d[s]);
+                }
+                pcr_level<1>(aa, b, cc, d);
+                pcr_level<2>(aa, b, cc, d);
+                pcr_level<4>(aa, b, cc, d);
+                pcr_level<8>(aa, b, cc, d);
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    x[s][M - 1] = d[s] * recip(b[s]);
+                    const double xl = before<1>(x[s][M - 1]);
+#pragma unroll
+                    for (int j = M - 2; j >= 0; --j)
+                        x[s][j] = fma(cr[s][j], x[s][j + 1], fma(fr[s][j], xl, dr[s][j]));
+                }
             }
         }
     }
     double acc = 0.0;
-    bool finite = true;
+    bool bad = false;
+    if (item < a.m) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int i = lane + 64 * j;
-        if (i < n) {
-            finite = finite && isfinite(u[j]) && isfinite(v[j]);
-            if (a.u_out) {
-                a.u_out[(size_t)item * n + i] = u[j];
-                a.v_out[(size_t)item * n + i] = v[j];
-            }
-            if (a.y) {
-                if (a.obs & 1) {
-                    const double e = a.y[i] - u[j];
-                    acc += e * e;
+        for (int j = 0; j < M; ++j) {
+            const int i = i0 + j;
+            if (i < n) {
+                bad = bad || !isfinite(x[0][j]) || !isfinite(x[1][j]);
+                if (a.u_out) {
+                    a.u_out[(size_t)item * n + i] = x[0][j];
+                    a.v_out[(size_t)item * n + i] = x[1][j];
                 }
-                if (a.obs & 2) {
-                    const double e = a.y[n + i] - v[j];
-                    acc += e * e;
+                if (a.y) {
+                    if (a.obs & 1) {
+                        const double e = a.y[i] - x[0][j];
+                        acc += e * e;
+                    }
+                    if (a.obs & 2) {
+                        const double e = a.y[n + i] - x[1][j];
+                        acc += e * e;
+                    }
                 }
             }
         }
     }
-    if (st == 0 && __any(!finite))
+    const bool any_bad = (__ballot(bad) >> (kLanes * sub)) & 0xFFFFull;
+    if (st == 0 && any_bad)
         st = RD_ST_NONFINITE;
-    acc = wave_sum(acc);
-    if (lane == 0) {
+    acc = item_sum(acc);
+    if (lane == kLanes - 1 && item < a.m) {
         if (a.status)
             a.status[item] = st;
         if (a.phi)
@@ -258,7 +276,19 @@ hipError_t launch_solve(const Args &a, hipStream_t s)
 {
     if (a.m <= 0)
         return hipSuccess;
-    hipLaunchKernelGGL(k_g1d_solve, dim3(a.m), dim3(64), 0, s, a);
+    // the fewest rows per lane that hold n cells
+    const dim3 grid((a.m + 64 / kLanes - 1) / (64 / kLanes)), block(64);
+    switch ((a.n + kLanes - 1) / kLanes) {
+    case 1: hipLaunchKernelGGL(k_g1d_solve<1>, grid, block, 0, s, a); break;
+    case 2: hipLaunchKernelGGL(k_g1d_solve<2>, grid, block, 0, s, a); break;
+    case 3: hipLaunchKernelGGL(k_g1d_solve<3>, grid, block, 0, s, a); break;
+    case 4: hipLaunchKernelGGL(k_g1d_solve<4>, grid, block, 0, s, a); break;
+    case 5: hipLaunchKernelGGL(k_g1d_solve<5>, grid, block, 0, s, a); break;
+    case 6: hipLaunchKernelGGL(k_g1d_solve<6>, grid, block, 0, s, a); break;
+    case 7: hipLaunchKernelGGL(k_g1d_solve<7>, grid, block, 0, s, a); break;
+    case 8: hipLaunchKernelGGL(k_g1d_solve<8>, grid, block, 0, s, a); break;
+    default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 
@@ -317,7 +347,7 @@ g1d::Args base_args(const g1d_problem *p)
     a.obs = d.obs;
     a.tau = d.tau;
     a.inv_tau = 1.0 / d.tau;
-    a.T = (double)d.n_steps * d.tau;
+    a.inv_T = 1.0 / ((double)d.n_steps * d.tau);
     a.rho_T = d.rho_T;
     a.a = d.theta[0];
     a.b = d.theta[1];
