@@ -1147,6 +1147,7 @@ __global__ __launch_bounds__(N *N / R) void k_solve_streamed(SolveArgs a)
 }  // namespace rd
 
 #include "rd_pcg.hpp"
+#include "rd_cg32.hpp"
 
 namespace rd {
 
@@ -2182,7 +2183,7 @@ hipError_t launch_fill_u32(unsigned *p, unsigned v, int count, hipStream_t s)
 // fit the VGPR budget of the workgroup size.
 namespace {
 
-enum Kind { kNone, kResident, kStreamed, kCoop, kSpectral, kSpectralGroup };
+enum Kind { kNone, kCg32, kStreamed, kCoop, kSpectral, kSpectralGroup };
 
 Kind tile_kind(int n, int precision, int cpt)
 {
@@ -2200,9 +2201,9 @@ Kind tile_kind(int n, int precision, int cpt)
             return kStreamed;
     } else {
         // (32^2 in FP64: few iterations to save, and callers compare it with
-        // plain CG stopped at the same tolerance)
+        // plain CG stopped at the same tolerance; one kernel serves every tile)
         if (n == 32 && (cpt == 4 || cpt == 8 || cpt == 16))
-            return kResident;
+            return kCg32;
         if ((n == 64 && (cpt == 8 || cpt == 16)) || (n == 128 && cpt == 32))
             return kSpectral;
         if (n == 256 && cpt == 128)
@@ -2211,10 +2212,9 @@ Kind tile_kind(int n, int precision, int cpt)
     return kNone;
 }
 
-template <int N, int R, typename Real>
-hipError_t go_resident(const SolveArgs &a, int wgs, hipStream_t s)
+hipError_t go_cg32(const SolveArgs &a, int wgs, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_solve_resident<N, R, Real>), dim3(wgs), dim3(N * N / R), 0, s, a);
+    hipLaunchKernelGGL(cg32::k_solve_cg32, dim3(wgs), dim3(cg32::T), 0, s, a);
     return hipGetLastError();
 }
 
@@ -2266,6 +2266,8 @@ size_t solve_slot_bytes(int n, int precision, int cpt)
 {
     if (tile_kind(n, precision, cpt) == kCoop)  // one member's strip: 4 arrays
         return (size_t)4 * kCoopStrip * kCoopN * sizeof(float);
+    if (tile_kind(n, precision, cpt) == kCg32)
+        return 256;  // nothing is kept there
     if (tile_kind(n, precision, cpt) == kSpectralGroup)
         return pcg::slot_bytes<pcg::S256>(precision != 0);
     if (tile_kind(n, precision, cpt) == kSpectral)
@@ -2289,14 +2291,13 @@ static int occupancy(K kernel, int threads)
 
 int solve_wgs_per_cu(int n, int precision, int cpt)
 {
-#define RD_OCC_R(NN, RR, T)                                                     \
-    if (n == NN && cpt == RR)                                                   \
-        return occupancy(k_solve_resident<NN, RR, T>, NN * NN / RR);
 #define RD_OCC_S(NN, RR, T)                                                     \
     if (n == NN && cpt == RR)                                                   \
         return occupancy(k_solve_streamed<NN, RR, T>, NN * NN / RR);
     if (tile_kind(n, precision, cpt) == kCoop)
         return occupancy(k_solve_coop, kCoopThreads);
+    if (tile_kind(n, precision, cpt) == kCg32)
+        return occupancy(cg32::k_solve_cg32, cg32::T);
     if (tile_kind(n, precision, cpt) == kSpectralGroup)
         return precision ? occupancy(pcg::k_solve_group<true>, pcg::S256::T)
                          : occupancy(pcg::k_solve_group<false>, pcg::S256::T);
@@ -2308,10 +2309,8 @@ int solve_wgs_per_cu(int n, int precision, int cpt)
     if (precision == 0) {
         RD_OCC_S(256, 64, float) RD_OCC_S(256, 128, float)
     } else {
-        RD_OCC_R(32, 4, double) RD_OCC_R(32, 8, double) RD_OCC_R(32, 16, double)
         RD_OCC_S(256, 128, double)
     }
-#undef RD_OCC_R
 #undef RD_OCC_S
     return 1;
 }
@@ -2397,7 +2396,7 @@ hipError_t launch_solve_class(int n, int precision, const SolveArgs &a, int wgs,
         a.gws_stride < solve_slot_bytes(n, precision, default_cpt(n, precision)))
         return hipErrorInvalidValue;
     if (n == 32 && precision)
-        return go_resident<32, 8, double>(a, wgs, s);
+        return go_cg32(a, wgs, s);
     spectral(n, precision, [&](auto kernel, int threads) {
         hipLaunchKernelGGL(kernel, dim3(wgs), dim3(threads), 0, s, a);
     });
@@ -2423,14 +2422,13 @@ hipError_t launch_solve(int n, int precision, TileChoice tile, const SolveArgs &
     // tiles also keep their strip arrays there).
     if (!a.gws || wgs > a.gws_slots || a.gws_stride < solve_slot_bytes(n, precision, cpt))
         return hipErrorInvalidValue;
-#define RD_RES(NN, RR, T)                                     \
-    if (n == NN && cpt == RR)                                 \
-        return go_resident<NN, RR, T>(a, wgs, s);
 #define RD_STR(NN, RR, T)                                     \
     if (n == NN && cpt == RR)                                 \
         return go_streamed<NN, RR, T>(a, wgs, s);
     if (tile_kind(n, precision, cpt) == kCoop)
         return launch_solve_coop(a, wgs, s);
+    if (tile_kind(n, precision, cpt) == kCg32)
+        return go_cg32(a, wgs, s);
     if (tile_kind(n, precision, cpt) == kSpectralGroup)
         return launch_solve_group(precision, a, wgs, false, s);
     if (tile_kind(n, precision, cpt) == kSpectral) {
@@ -2442,10 +2440,8 @@ hipError_t launch_solve(int n, int precision, TileChoice tile, const SolveArgs &
     if (precision == 0) {
         RD_STR(256, 64, float) RD_STR(256, 128, float)
     } else {
-        RD_RES(32, 4, double) RD_RES(32, 8, double) RD_RES(32, 16, double)
         RD_STR(256, 128, double)
     }
-#undef RD_RES
 #undef RD_STR
     return hipErrorInvalidValue;
 }
