@@ -10,13 +10,12 @@
 // consecutive columns of one strip row, so every LDS/global row access is
 // contiguous across lanes.
 //
-// Resident variant (N <= 128): the strip arrays (u, v, the two reaction
-// diagonals, the CG residual and A p) live in VGPRs; only the CG search
-// direction p is shared, through LDS, for the 5-point stencil, and v is
-// parked in LDS while the u system is solved.  The whole
-// solve touches HBM only to read the initial fields and the data once.
-// Streamed variant (large N or FP64 at N = 128): the same algorithm with
-// the strip arrays and p in a per-workgroup global-memory slot.
+// This file holds the tiled solver, which keeps the strip arrays and p in a
+// per-workgroup global-memory slot (256^2), the cooperative one (256^2 by groups
+// of workgroups with the arrays in registers), the queue orders and the
+// dispatch; rd_pcg.hpp and rd_pcg_group.hpp hold the spectrally preconditioned
+// solver of the other sizes and of the default 256^2 tile, rd_cg32.hpp the FP64
+// one of 32^2.
 //
 // Precision: Real = float keeps the fields and CG vectors in FP32 and every
 // dot product, CG scalar and the misfit in FP64; Real = double is FP64
@@ -145,87 +144,14 @@ __device__ __forceinline__ void sweep_nsum(const Real *P, const Geo<N, R> &g, F 
     }
 }
 
-// sweep() over two arrays with the same layout at once: f(k, p_c, t(p),
-// q_c, t(q)).
-template <int N, int R, int U, typename Real, typename F>
-__device__ __forceinline__ void sweep_pair(const Real *P, const Real *Q, const Geo<N, R> &g, F &&f)
-{
-    Real cur = P[g.j0 * N + g.i], qcur = Q[g.j0 * N + g.i];
-    Real south = (g.j0 > 0) ? P[(g.j0 - 1) * N + g.i] : cur;
-    Real qsouth = (g.j0 > 0) ? Q[(g.j0 - 1) * N + g.i] : qcur;
-#pragma unroll U
-    for (int k = 0; k < R; ++k) {
-        const int j = g.j0 + k;
-        const bool in = k + 1 < R || j + 1 < N;
-        const Real north = in ? P[(j + 1) * N + g.i] : cur;
-        const Real qnorth = in ? Q[(j + 1) * N + g.i] : qcur;
-        const Real t = ((cur - P[j * N + g.iw]) + (cur - P[j * N + g.ie])) +
-                       ((cur - south) + (cur - north));
-        const Real qt = ((qcur - Q[j * N + g.iw]) + (qcur - Q[j * N + g.ie])) +
-                        ((qcur - qsouth) + (qcur - qnorth));
-        f(k, cur, t, qcur, qt);
-        south = cur;
-        cur = north;
-        qsouth = qcur;
-        qcur = qnorth;
-        RD_GROUP_FENCE(k)
-    }
-}
-
-// sweep_pair() with the first array's differences formed and summed in FP64:
-// f(k, p_c, t64(p), q_c, t(q)).  The differences of FP32 values are exact
-// in FP64, so t64 carries no rounding error to speak of; the residual of a
-// compensated field needs it (the FP32 sum of the four differences, scaled
-// by c, rounds at about 2^-24 of the diffusion term, which lies above
-// rtol |b| for rtol 1e-9).
-template <int N, int R, int U, typename F>
-__device__ __forceinline__ void sweep_pair64(const float *P, const float *Q, const Geo<N, R> &g,
-                                             F &&f)
-{
-    float cur = P[g.j0 * N + g.i], qcur = Q[g.j0 * N + g.i];
-    double cur64 = cur;
-    double south64 = (g.j0 > 0) ? (double)P[(g.j0 - 1) * N + g.i] : cur64;
-    float qsouth = (g.j0 > 0) ? Q[(g.j0 - 1) * N + g.i] : qcur;
-#pragma unroll U
-    for (int k = 0; k < R; ++k) {
-        const int j = g.j0 + k;
-        const bool in = k + 1 < R || j + 1 < N;
-        const float north = in ? P[(j + 1) * N + g.i] : cur;
-        const float qnorth = in ? Q[(j + 1) * N + g.i] : qcur;
-        const double north64 = north;
-        const double t64 = ((cur64 - (double)P[j * N + g.iw]) + (cur64 - (double)P[j * N + g.ie])) +
-                           ((cur64 - south64) + (cur64 - north64));
-        const float qt = ((qcur - Q[j * N + g.iw]) + (qcur - Q[j * N + g.ie])) +
-                         ((qcur - qsouth) + (qcur - qnorth));
-        f(k, cur, t64, qcur, qt);
-        south64 = cur64;
-        cur64 = north64;
-        cur = north;
-        qsouth = qcur;
-        qcur = qnorth;
-        RD_GROUP_FENCE(k)
-    }
-}
-
 // P <- own cells of a global array (src = own-cell pointer, cell k at
-// src[k N]).  kLds: P is in LDS (resident variant).  When the 64 lanes of a wave own 64 consecutive words of every
-// strip row (N >= 64) the copy uses direct global->LDS loads, which need no
-// VGPRs and keep all R loads in flight at once; otherwise it goes through
-// registers.  The caller places a barrier before the stencil reads P.
-template <int N, int R, int U, bool kLds, typename Real>
-__device__ __forceinline__ void copy_to_lds(const Real *src, Real *P, const Geo<N, R> &g)
+// src[k N]).  The caller places a barrier before the stencil reads P.
+template <int N, int R, int U, typename Real>
+__device__ __forceinline__ void copy_strip(const Real *src, Real *P, const Geo<N, R> &g)
 {
-    if constexpr (kLds && N >= kWave && sizeof(Real) == 4) {
-        const int row0 = uniform(g.j0 * N + (g.i & ~(kWave - 1)));
-#pragma unroll
-        for (int k = 0; k < R; ++k)
-            __builtin_amdgcn_global_load_lds(src + k * N, P + row0 + k * N, 4, 0, 0);
-        __builtin_amdgcn_s_waitcnt(0);  // the LDS writes have landed
-    } else {
 #pragma unroll U
-        for (int k = 0; k < R; ++k)
-            P[g.idx(k)] = src[k * N];
-    }
+    for (int k = 0; k < R; ++k)
+        P[g.idx(k)] = src[k * N];
 }
 
 // LDS reduction slots: [0, 4W) set-up, [4W, 5W) p.q, [5W, 6W) r.r,
@@ -257,11 +183,6 @@ __device__ __forceinline__ Real step_ratio(double num, double den)
     else
         return uniform(num / den);
 }
-
-// Squared CG tolerance below which the resident FP32 solve evaluates its
-// step residual in FP64 (rtol < 3e-8: ten times the FP32 evaluation's
-// rounding floor relative to |b|).
-constexpr double kRes64Rtol2 = 9e-16;
 
 template <typename Real>
 struct Compensated {
@@ -297,26 +218,17 @@ __device__ __forceinline__ void two_sum(float a, float b, float &s, float &e)
 // second order.  npred = 0: d0 = 0.  The system and the stopping test are
 // unchanged: |r| <= rtol |b| on the recursively updated residual.  `quiet`
 // returns whether r0 itself met the tolerance (the field did not move).
-//
-// kFuse (resident FP32): on entry the other species' field is still in
-// registers (Sreg) and the LDS stash behind S is free.  The residuals of hi
-// and of lo are then formed in one pass, lo staged in the stash, and Sreg
-// is parked in the stash afterwards (S reads it from there on).
-template <int N, int R, int U, int NW, bool kLds, int kSp, bool kFuse = false, bool kPred2 = false,
-          typename Real, class Arr, class SArr>
+template <int N, int R, int U, int NW, int kSp, typename Real, class Arr, class SArr>
 __device__ int cg_solve(const Arr &hi, const SArr &S, Arr &r, Arr &q, Arr &d, Real inv_dt, Real c,
                         Real src, Real dl, Real gam, double rtol2, int maxit, Real *P,
                         const Real *lo, const Real *H1, const Real *H2, int npred, double *red,
-                        const Geo<N, R> &g, int &it_acc, int &quiet, const Arr *Sreg = nullptr,
-                        Real *stash = nullptr, const Real *Slo = nullptr)
+                        const Geo<N, R> &g, int &it_acc, int &quiet)
 {
     constexpr bool comp = Compensated<Real>::on;
-    static_assert(!kFuse || (comp && kLds), "the fused set-up is for resident FP32 solves");
     // the two-increment start reads the histories a group of kGroup cells at
     // the group's first cell and indexes its group buffers with k % kGroup,
-    // a constant only when the unroll factor is a multiple of the group (the
-    // other grouped loops run only fully unrolled)
-    static_assert(!kPred2 || (U % kGroup == 0 && R % kGroup == 0), "unroll by whole groups");
+    // a constant only when the unroll factor is a multiple of the group
+    static_assert(U % kGroup == 0 && R % kGroup == 0, "unroll by whole groups");
     // e(k) and sigma(k) = 1/dt + e(k)
     const Real e0 = uniform(kSp == 0 ? dl + gam : dl);
     const Real s0 = uniform(e0 + inv_dt);
@@ -332,28 +244,6 @@ __device__ int cg_solve(const Arr &hi, const SArr &S, Arr &r, Arr &q, Arr &d, Re
         else
             return s0 + gam * (S[k] * S[k]);
     };
-    // sigma_at() for a sweep that visits k = 0 .. R-1 in order (the set-up
-    // sweeps): with the sweep fully unrolled, S (the LDS stash in FP32
-    // tiles) is read a pinned group of cells at a time, at the group's
-    // first cell; read at each cell, every read was waited for before the
-    // next.
-    Real sgrp[kGroup];
-    auto sigma_seq = [&](int k) -> Real {
-        if constexpr (U == R) {
-            if (k % kGroup == 0) {
-#pragma unroll
-                for (int j = 0; j < kGroup; ++j)
-                    sgrp[j] = k + j < R ? S[k + j] : Real(0);
-            }
-            const Real sk = sgrp[k % kGroup];
-            if constexpr (kSp == 0)
-                return s0 - gam * (hi[k] * sk);
-            else
-                return s0 + gam * (sk * sk);
-        } else {
-            return sigma_at(k);
-        }
-    };
     // sigma + 4c, the diagonal of the neighbour-sum form
     const Real s04 = uniform(s0 + Real(4) * c);
     auto sigma4_at = [&](int k) -> Real {
@@ -363,76 +253,6 @@ __device__ int cg_solve(const Arr &hi, const SArr &S, Arr &r, Arr &q, Arr &d, Re
             return s04 + gam * (S[k] * S[k]);
     };
     double bb = 0.0, rr = 0.0;
-    if constexpr (kFuse) {
-        const Arr &Sr = *Sreg;
-        const bool use64 = rtol2 < kRes64Rtol2;
-        // the stash's last reads (own cells) are complete before lo lands there
-        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-        copy_to_lds<N, R, U, kLds>(lo + g.off(), stash, g);
-#pragma unroll U
-        for (int k = 0; k < R; ++k) {
-            P[g.idx(k)] = hi[k];
-            RD_GROUP_FENCE(k)
-        }
-        // r0 = src - e x - c t(x) for x = hi + lo.  Evaluated in FP32 its
-        // rounding (about 2^-24 of the reaction and diffusion terms, 2-3e-9
-        // of |b|) lies above rtol |b| once rtol drops below about 3e-8, and
-        // CG would spend iterations on that noise every step; there it is
-        // evaluated in FP64, with e from the other field's hi + lo too.
-        // At looser tolerances the FP32 form costs less.  The operator of the
-        // CG itself stays FP32: its rounding enters only through the
-        // increment, far below the tolerance.
-        if (use64) {
-            // the other field's low part (level n, in the slot; q is free
-            // until the predictor).  Loaded here, not ahead of the copy of
-            // lo: held across it, the 16 registers made the compiler spill
-            // inside the CG loop.
-            const int o = g.off();
-#pragma unroll U
-            for (int k = 0; k < R; ++k)
-                q[k] = Slo[o + k * N];
-            __syncthreads();
-            const double e0d = e0, gamd = gam, srcd = src, cd = c;
-            sweep_pair64<N, R, U>(P, stash, g, [&](int k, Real own, double t64, Real lown, Real lt) {
-                const double x64 = (double)own + (double)lown;
-                const double s64 = (double)Sr[k] + (double)q[k];
-                const double e = kSp == 0 ? e0d - gamd * (x64 * s64) : e0d + gamd * (s64 * s64);
-                const Real b = own * inv_dt + src;
-                const double res64 = (srcd - e * x64) - cd * (t64 + (double)lt);
-                Real res = (Real)res64;
-                RD_PIN(res);
-                r[k] = res;
-                bb += (double)b * (double)b;
-                rr += (double)res * (double)res;
-                RD_PIN(bb);
-                RD_PIN(rr);
-            });
-        } else {
-            __syncthreads();
-            auto e_reg = [&](int k) -> Real {
-                if constexpr (kSp == 0)
-                    return e0 - gam * (hi[k] * Sr[k]);
-                else
-                    return e0 + gam * (Sr[k] * Sr[k]);
-            };
-            sweep_pair<N, R, U>(P, stash, g, [&](int k, Real own, Real t, Real lown, Real lt) {
-                const Real e = e_reg(k);
-                const Real b = own * inv_dt + src;
-                Real res = src - e * own - c * t;
-                res = res - (e * lown + c * lt);
-                RD_PIN(res);
-                r[k] = res;
-                bb += (double)b * (double)b;
-                rr += (double)res * (double)res;
-                RD_PIN(bb);
-                RD_PIN(rr);
-            });
-        }
-        __syncthreads();  // every stencil read of P and of the stash is done
-#pragma unroll U
-        for (int k = 0; k < R; ++k)
-            stash[g.idx(k)] = Sr[k];
-    } else {
 #pragma unroll U
     for (int k = 0; k < R; ++k) {
         P[g.idx(k)] = hi[k];
@@ -457,7 +277,7 @@ __device__ int cg_solve(const Arr &hi, const SArr &S, Arr &r, Arr &q, Arr &d, Re
     if constexpr (comp) {
         // the low part's share of A x
         __syncthreads();
-        copy_to_lds<N, R, U, kLds>(lo + g.off(), P, g);
+        copy_strip<N, R, U>(lo + g.off(), P, g);
         __syncthreads();
         sweep<N, R, U>(P, g, [&](int k, Real own, Real t) {
             Real res = r[k] - (e_at(k) * own + c * t);
@@ -467,15 +287,13 @@ __device__ int cg_solve(const Arr &hi, const SArr &S, Arr &r, Arr &q, Arr &d, Re
             RD_PIN(rr);
         });
     }
-    }
     bool rr_pending = false;
-    if (kPred2 && npred == 2) {
+    if (npred == 2) {
         // Gram entries (H_i, A H_j) and (H_i, r0) from two stencil sweeps;
         // then d0 = w1 H1 + w2 H2 goes to P and one more sweep forms A d0.
         // No stencil result is kept across sweeps (register pressure).
-        if constexpr (!kFuse)
-            __syncthreads();  // every stencil read of P is done
-        copy_to_lds<N, R, U, kLds>(H1 + g.off(), P, g);
+        __syncthreads();  // every stencil read of P is done
+        copy_strip<N, R, U>(H1 + g.off(), P, g);
         __syncthreads();
         const Real *h2 = H2 + g.off();
         // H2's own cells are loaded a group of cells at a time, at the
@@ -490,7 +308,7 @@ __device__ int cg_solve(const Arr &hi, const SArr &S, Arr &r, Arr &q, Arr &d, Re
                 for (int j = 0; j < kGroup; ++j)
                     h2g[j] = k + j < R ? h2[(k + j) * N] : Real(0);
             }
-            Real w = c * t + sigma_seq(k) * own;  // (A H1) at the cell
+            Real w = c * t + sigma_at(k) * own;  // (A H1) at the cell
             RD_PIN(w);
             const double wd = (double)w;
             g11 += (double)own * wd;
@@ -501,11 +319,11 @@ __device__ int cg_solve(const Arr &hi, const SArr &S, Arr &r, Arr &q, Arr &d, Re
             RD_PIN(b1);
         });
         __syncthreads();  // every stencil read of H1 is done
-        copy_to_lds<N, R, U, kLds>(h2, P, g);
+        copy_strip<N, R, U>(h2, P, g);
         __syncthreads();
         double g22 = 0.0, b2 = 0.0;
         sweep<N, R, U>(P, g, [&](int k, Real own, Real t) {
-            Real w = c * t + sigma_seq(k) * own;  // (A H2) at the cell
+            Real w = c * t + sigma_at(k) * own;  // (A H2) at the cell
             RD_PIN(w);
             g22 += (double)own * (double)w;
             b2 += (double)own * (double)r[k];
@@ -552,7 +370,7 @@ __device__ int cg_solve(const Arr &hi, const SArr &S, Arr &r, Arr &q, Arr &d, Re
         }
         __syncthreads();
         sweep<N, R, U>(P, g, [&](int k, Real own, Real t) {
-            Real w = c * t + sigma_seq(k) * own;  // (A d0) at the cell
+            Real w = c * t + sigma_at(k) * own;  // (A d0) at the cell
             RD_PIN(w);
             r[k] = r[k] - w;
         });
@@ -562,13 +380,12 @@ __device__ int cg_solve(const Arr &hi, const SArr &S, Arr &r, Arr &q, Arr &d, Re
         // |r0 - A d0|^2 is summed from the updated r in the first CG sweep
         rr_pending = true;
     } else if (npred == 1) {
-        if constexpr (!kFuse)
-            __syncthreads();  // every stencil read of P is done
-        copy_to_lds<N, R, U, kLds>(H1 + g.off(), P, g);
+        __syncthreads();  // every stencil read of P is done
+        copy_strip<N, R, U>(H1 + g.off(), P, g);
         __syncthreads();
         double rw = 0.0, ww = 0.0;
         sweep<N, R, U>(P, g, [&](int k, Real own, Real t) {
-            Real w = c * t + sigma_seq(k) * own;  // (A H) at the cell
+            Real w = c * t + sigma_at(k) * own;  // (A H) at the cell
             RD_PIN(w);
             q[k] = w;
             rw += (double)r[k] * (double)w;
@@ -584,19 +401,9 @@ __device__ int cg_solve(const Arr &hi, const SArr &S, Arr &r, Arr &q, Arr &d, Re
         ww = v4[3];
         quiet = !(rr > rtol2 * bb);
         const Real w = uniform((Real)((ww > 0.0 && finite(rw)) ? rw / ww : 0.0));
-        Real pg[kGroup];  // H's own cells, a group at a time (as in the CG loop)
 #pragma unroll U
         for (int k = 0; k < R; ++k) {
-            if constexpr (U == R) {
-                if (k % kGroup == 0) {
-#pragma unroll
-                    for (int j = 0; j < kGroup; ++j)
-                        pg[j] = k + j < R ? P[g.idx(k + j)] : Real(0);
-                }
-                d[k] = w * pg[k % kGroup];
-            } else {
-                d[k] = w * P[g.idx(k)];
-            }
+            d[k] = w * P[g.idx(k)];
             r[k] = r[k] - w * q[k];
             RD_GROUP_FENCE(k)
         }
@@ -693,33 +500,13 @@ __device__ int cg_solve(const Arr &hi, const SArr &S, Arr &r, Arr &q, Arr &d, Re
         }
         const Real bt = step_ratio<Real>(rn, rr);
         // d += alpha p_old and p = r + beta p_old (own cells only; the
-        // stencil reads of p finished before the p.q barrier).  Fully
-        // unrolled, the reads of a group of cells are issued together
-        // before its writes: read cell by cell, each read waited for the
-        // write before it (the compiler does not separate the cells'
-        // addresses), one LDS round trip per cell on every wave's path.
-        if constexpr (U == R) {
-            Real pg[kGroup];
-#pragma unroll
-            for (int k = 0; k < R; ++k) {
-                if (k % kGroup == 0) {
-#pragma unroll
-                    for (int j = 0; j < kGroup; ++j)
-                        pg[j] = k + j < R ? P[g.idx(k + j)] : Real(0);
-                }
-                const Real p = pg[k % kGroup];
-                d[k] = d[k] + a * p;
-                P[g.idx(k)] = r[k] + bt * p;
-                RD_GROUP_FENCE(k)
-            }
-        } else {
+        // stencil reads of p finished before the p.q barrier)
 #pragma unroll U
-            for (int k = 0; k < R; ++k) {
-                const Real p = P[g.idx(k)];
-                d[k] = d[k] + a * p;
-                P[g.idx(k)] = r[k] + bt * p;
-                RD_GROUP_FENCE(k)
-            }
+        for (int k = 0; k < R; ++k) {
+            const Real p = P[g.idx(k)];
+            d[k] = d[k] + a * p;
+            P[g.idx(k)] = r[k] + bt * p;
+            RD_GROUP_FENCE(k)
         }
         rr = rn;
     }
@@ -743,59 +530,23 @@ __device__ __forceinline__ void fold(Arr &hi, Arr &d, Real *lo, Real *H, const G
 {
     constexpr bool comp = Compensated<Real>::on;
     const int o = g.off();
-    if constexpr (R * sizeof(Real) > 32 * sizeof(float)) {
-        // long strips (streamed variant): one pass, the loads overlap with
-        // the other workgroups' work instead
 #pragma unroll U
-        for (int k = 0; k < R; ++k) {
-            const Real dk = kDGlobal ? H[o + k * N] : d[k];
-            if constexpr (comp) {
-                float s, e;
-                two_sum(hi[k], dk, s, e);
-                const float lk = lo[o + k * N] + e;
-                const float nh = s + lk;
-                hi[k] = nh;
-                lo[o + k * N] = lk - (nh - s);
-            } else {
-                hi[k] = hi[k] + dk;
-            }
-            if (!kDGlobal && H)
-                H[o + k * N] = dk;
-            if (acc)
-                *acc += (double)dk * (double)dk;
-        }
-        return;
-    }
-    Real l[R], dd[R];
-#pragma unroll
     for (int k = 0; k < R; ++k) {
-        if constexpr (comp)
-            l[k] = lo[o + k * N];
-        dd[k] = kDGlobal ? H[o + k * N] : d[k];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-        if constexpr (comp)
-            RD_PIN(l[k]);
-        RD_PIN(dd[k]);
-    }
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
+        const Real dk = kDGlobal ? H[o + k * N] : d[k];
         if constexpr (comp) {
             float s, e;
-            two_sum(hi[k], dd[k], s, e);
-            const float lk = l[k] + e;
+            two_sum(hi[k], dk, s, e);
+            const float lk = lo[o + k * N] + e;
             const float nh = s + lk;
             hi[k] = nh;
             lo[o + k * N] = lk - (nh - s);
         } else {
-            hi[k] = hi[k] + dd[k];
+            hi[k] = hi[k] + dk;
         }
         if (!kDGlobal && H)
-            H[o + k * N] = dd[k];
+            H[o + k * N] = dk;
         if (acc)
-            *acc += (double)dd[k] * (double)dd[k];
+            *acc += (double)dk * (double)dk;
     }
 }
 
@@ -825,26 +576,18 @@ struct SlotLayout {
 //   (1/dt + 2 r_n + g u^2)       v' - d rho_n^-2 Lap v' = v/dt + g b
 // Both systems use the fields of level n only, so they are solved one after
 // the other with one set of CG work arrays (r, q, d); u is advanced only
-// after the v solve, which needs u^n.  Resident variant (kLds): P and
-// `stash` are in LDS and the stash parks the field not being solved for
-// (v^n during the u solve, u^n during the v solve), so that a solve keeps
-// four strip arrays in VGPRs.  Streamed variant: all arrays are global and
-// `stash` is null.  `slot` is the item's global slot (SlotLayout).
-//
-// kPred2: the CG start vector uses the increments of the last two steps
-// (cg_solve, npred = 2); otherwise the last one only.  Kernels that inline
-// several grid classes keep the one-increment start (its fewer live values
-// keep their register spills down).
-template <int N, int R, int U, int NW, bool kLds, typename Real, bool kPred2, class Arr>
+// after the v solve, which needs u^n.  All arrays are in the item's global slot
+// (`slot`, SlotLayout).
 //
 // steady_tt > 0 (Sec. 3.1.2): stop after the first step whose discrete time
 // derivative has an L2 norm over the unit square below the threshold,
 // sqrt(h^2 sum (du^2 + dv^2)) / dt < tol with h = 1/N, i.e. sum (du^2 + dv^2)
 // < (tol dt N)^2 with steady_tt = tol dt; n_steps is then the cap, and an
 // item that reaches it gets kStNotSteady.  `steps` returns the steps taken.
+template <int N, int R, int U, int NW, typename Real, class Arr>
 __device__ int integrate(Arr &xu, Arr &xv, Arr &r, Arr &q, Arr &d, const double th[4],
                          const GridDev &gd, double dt, int n_steps, double rtol2, int maxit,
-                         Real *P, Real *stash, Real *slot, double *red, const Geo<N, R> &g,
+                         Real *P, Real *slot, double *red, const Geo<N, R> &g,
                          int &itu, int &itv, double steady_tt, int &steps)
 {
     using L = SlotLayout<Real>;
@@ -880,64 +623,16 @@ __device__ int integrate(Arr &xu, Arr &xv, Arr &r, Arr &q, Arr &d, const double 
         Real *const hv_new = slot + L::hist(1, kn) * N * N;
         const Real *const hu_last = slot + L::hist(0, kn ^ 1) * N * N;
         const Real *const hv_last = slot + L::hist(1, kn ^ 1) * N * N;
-        const int npred_u = (s == 0 || quiet_u) ? 0 : (s == 1 || !kPred2 || last_u < 2) ? 1 : 2;
-        const int npred_v = (s == 0 || quiet_v) ? 0 : (s == 1 || !kPred2 || last_v < 2) ? 1 : 2;
+        const int npred_u = (s == 0 || quiet_u) ? 0 : (s == 1 || last_u < 2) ? 1 : 2;
+        const int npred_v = (s == 0 || quiet_v) ? 0 : (s == 1 || last_v < 2) ? 1 : 2;
         const int itu0 = itu, itv0 = itv;
-        if constexpr (kLds && comp) {
-            // FP32: each solve parks the other field itself, after its fused
-            // residual pass has used the stash for the low part
-            LdsArr<Real, N> sv{stash + g.idx(0)};
-            st = cg_solve<N, R, U, NW, kLds, 0, true, kPred2>(xu, sv, r, q, d, inv_dt, cu, src_u, dl, gam,
-                                                      rtol2, maxit, P, lo_u, hu_last, hu_new,
-                                                      npred_u, red, g, itu, quiet_u, &xv, stash,
-                                                      lo_v);
-#pragma unroll U
-            for (int k = 0; k < R; ++k)
-                xv[k] = sv[k];
-            if (st)
-                break;
-            store_increment<N, R, U>(d, hu_new, g);
-            st = cg_solve<N, R, U, NW, kLds, 1, true, kPred2>(xv, sv, r, q, d, inv_dt, cv, src_v, dl, gam,
-                                                      rtol2, maxit, P, lo_v, hv_last, hv_new,
-                                                      npred_v, red, g, itv, quiet_v, &xu, stash,
-                                                      lo_u);
-#pragma unroll U
-            for (int k = 0; k < R; ++k)
-                xu[k] = sv[k];
-        } else if constexpr (kLds) {
-            LdsArr<Real, N> sv{stash + g.idx(0)};
-#pragma unroll U
-            for (int k = 0; k < R; ++k)
-                sv[k] = xv[k];
-            st = cg_solve<N, R, U, NW, kLds, 0, false, kPred2>(xu, sv, r, q, d, inv_dt, cu, src_u, dl, gam, rtol2,
-                                                maxit, P, lo_u, hu_last, hu_new, npred_u, red, g,
-                                                itu, quiet_u);
-#pragma unroll U
-            for (int k = 0; k < R; ++k) {
-                xv[k] = sv[k];
-                if (!st)
-                    sv[k] = xu[k];
-            }
-            if (st)
-                break;
-            store_increment<N, R, U>(d, hu_new, g);
-            st = cg_solve<N, R, U, NW, kLds, 1, false, kPred2>(xv, sv, r, q, d, inv_dt, cv, src_v, dl, gam, rtol2,
-                                                maxit, P, lo_v, hv_last, hv_new, npred_v, red, g,
-                                                itv, quiet_v);
-#pragma unroll U
-            for (int k = 0; k < R; ++k)
-                xu[k] = sv[k];
-        } else {
-            st = cg_solve<N, R, U, NW, kLds, 0, false, kPred2>(xu, xv, r, q, d, inv_dt, cu, src_u, dl, gam, rtol2,
-                                                maxit, P, lo_u, hu_last, hu_new, npred_u, red, g,
-                                                itu, quiet_u);
-            if (st)
-                break;
-            store_increment<N, R, U>(d, hu_new, g);
-            st = cg_solve<N, R, U, NW, kLds, 1, false, kPred2>(xv, xu, r, q, d, inv_dt, cv, src_v, dl, gam, rtol2,
-                                                maxit, P, lo_v, hv_last, hv_new, npred_v, red, g,
-                                                itv, quiet_v);
-        }
+        st = cg_solve<N, R, U, NW, 0>(xu, xv, r, q, d, inv_dt, cu, src_u, dl, gam, rtol2, maxit, P,
+                                      lo_u, hu_last, hu_new, npred_u, red, g, itu, quiet_u);
+        if (st)
+            break;
+        store_increment<N, R, U>(d, hu_new, g);
+        st = cg_solve<N, R, U, NW, 1>(xv, xu, r, q, d, inv_dt, cv, src_v, dl, gam, rtol2, maxit, P,
+                                      lo_v, hv_last, hv_new, npred_v, red, g, itv, quiet_v);
         if (st)
             break;
         steps = s + 1;
@@ -1061,28 +756,9 @@ __device__ __forceinline__ int item_grid(const SolveArgs &a, int c)
     return -1;
 }
 
-// One item, resident variant: P and stash are LDS arrays of at least N*N.
-template <int N, int R, typename Real, bool kPred2 = false>
-__device__ __forceinline__ void solve_item_resident(const SolveArgs &a, int c, const GridDev &gd,
-                                                    Real *P, Real *stash, double *red, Real *slot)
-{
-    constexpr int NW = (N * N / R) / kWave;
-    const Geo<N, R> g;
-    const double th[4] = {a.theta[4 * c], a.theta[4 * c + 1], a.theta[4 * c + 2],
-                          a.theta[4 * c + 3]};
-    RegArr<Real, R> xu, xv, r, q, d;
-    load_initial<N, R, R>(gd, xu, xv, slot, g);
-    int itu = 0, itv = 0, steps = 0;
-    const int st = integrate<N, R, R, NW, true, Real, kPred2>(xu, xv, r, q, d, th, gd, a.dt,
-                                                              a.n_steps, a.rtol2,
-                                                a.maxit, P, stash, slot, red, g, itu, itv,
-                                                a.steady_tt, steps);
-    finish_item<N, R, Real>(a, gd, c, xu, xv, st, itu, itv, slot, g, red, steps);
-}
-
 // One item, streamed variant: the strip arrays and p follow the SlotLayout
 // arrays in the workgroup's global slot.
-template <int N, int R, typename Real, bool kPred2 = false>
+template <int N, int R, typename Real>
 __device__ __forceinline__ void solve_item_streamed(const SolveArgs &a, int c, const GridDev &gd,
                                                     double *red, Real *slot)
 {
@@ -1099,31 +775,10 @@ __device__ __forceinline__ void solve_item_streamed(const SolveArgs &a, int c, c
                           a.theta[4 * c + 3]};
     load_initial<N, R, U>(gd, xu, xv, slot, g);
     int itu = 0, itv = 0, steps = 0;
-    const int st = integrate<N, R, U, NW, false, Real, kPred2>(xu, xv, r, q, d, th, gd, a.dt,
-                                                               a.n_steps, a.rtol2,
-                                                 a.maxit, P, (Real *)nullptr, slot, red, g, itu,
-                                                 itv, a.steady_tt, steps);
+    const int st = integrate<N, R, U, NW, Real>(xu, xv, r, q, d, th, gd, a.dt, a.n_steps, a.rtol2,
+                                                a.maxit, P, slot, red, g, itu, itv, a.steady_tt,
+                                                steps);
     finish_item<N, R, Real>(a, gd, c, xu, xv, st, itu, itv, slot, g, red, steps);
-}
-
-template <int N, int R, typename Real>
-__global__ __launch_bounds__(N *N / R) void k_solve_resident(SolveArgs a)
-{
-    constexpr int NW = (N * N / R) / kWave;
-    __shared__ Real P[N * N];
-    __shared__ Real stash[N * N];
-    __shared__ double red[Slots<NW>::total];
-    __shared__ int s_item;
-    Real *slot = (Real *)((char *)a.gws + (size_t)blockIdx.x * a.gws_stride);
-    for (int item = next_item(a.queue, &s_item); item < a.n_items;
-         item = next_item(a.queue, &s_item)) {
-        const int c = uniform(a.order ? a.order[item] : item);
-        if (!a.need || uniform(a.need[c])) {
-            const int gid = item_grid(a, c);
-            if (gid >= 0 && uniform(a.grids[gid].n) == N)
-                solve_item_resident<N, R, Real, true>(a, c, a.grids[gid], P, stash, red, slot);
-        }
-    }
 }
 
 template <int N, int R, typename Real>
@@ -1139,7 +794,7 @@ __global__ __launch_bounds__(N *N / R) void k_solve_streamed(SolveArgs a)
         if (!a.need || uniform(a.need[c])) {
             const int gid = item_grid(a, c);
             if (gid >= 0)
-                solve_item_streamed<N, R, Real, true>(a, c, a.grids[gid], red, slot);
+                solve_item_streamed<N, R, Real>(a, c, a.grids[gid], red, slot);
         }
     }
 }
@@ -1262,8 +917,7 @@ __global__ void k_note_cost(int n, const int *need, const int *iters, int *cost)
 // A single workgroup cannot hold a 256^2 item in VGPRs and LDS, and the
 // streamed variant (arrays in HBM) takes ~30 s per solve on one CU.  Here
 // member m of the group owns the horizontal strip of rows 64m .. 64m+63 and
-// keeps it resident exactly as the 128^2 kernel does (16 cells per thread,
-// 1024 threads); the 5-point stencil needs the neighbouring members' edge
+// keeps it in registers, p in LDS (16 cells per thread, 1024 threads); the 5-point stencil needs the neighbouring members' edge
 // rows, and CG's dot products need the group's sums.  Both go through a
 // per-group area of global memory with agent-coherent (sc1) loads and
 // stores.  A group exchange publishes each member's partial sums tagged
@@ -1645,10 +1299,9 @@ __device__ int cg_coop(const RegArr<float, kCoopR> &hi, const LdsArr<float, kCoo
     coop_sync(x);
     coop_fetch_halo(x, kFieldHi, P);
     __syncthreads();
-    // r0 in FP32 (hi pass, then lo pass).  The resident tiles evaluate it in
-    // FP64, which saves CG iterations at rtol 1e-9; here the extra registers
-    // of that evaluation made the compiler spill inside the CG loop, which
-    // cost more than the iterations saved.
+    // r0 in FP32 (hi pass, then lo pass).  Evaluated in FP64 it would save
+    // CG iterations at rtol 1e-9, but the extra registers made the compiler
+    // spill inside the CG loop, which cost more than the iterations saved.
     double bb = 0.0, rr = 0.0;
     const float *slp = Slo + g.off();
     const double e0d = e0, gamd = gam;
@@ -2179,8 +1832,7 @@ hipError_t launch_fill_u32(unsigned *p, unsigned v, int count, hipStream_t s)
 }
 
 // ---------------------------------------------------------------------------
-// Tile table.  Resident tiles exist where the strip arrays (6 x cpt values)
-// fit the VGPR budget of the workgroup size.
+// Tile table.
 namespace {
 
 enum Kind { kNone, kCg32, kStreamed, kCoop, kSpectral, kSpectralGroup };
