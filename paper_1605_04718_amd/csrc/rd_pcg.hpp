@@ -1083,6 +1083,8 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int c, const Grid
 #pragma unroll
     for (int i = 0; i < R; ++i)
         d[i] = 0.0f;
+    int moved = 0;   // the last system's increment may differ from zero
+    int zeroed = 0;  // increment buffers (2 species + buffer) known to hold zeros
     Scalars v;
     for (int n = 0; n < a.n_steps; ++n, rho_m2 = uniform(rho_m2 * decay)) {
         // buffer n & 1 holds the increment of step n - 2 and receives this one
@@ -1097,21 +1099,35 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int c, const Grid
             y.g = uniform(th2);
             const int fo = 2 * cur + sp, ft = 2 * cur + (1 - sp);
             double es;
-            // (FP32: d is the increment of the other species' last system)
-            if (sp == 0)
-                residual<0, !kFp64>(x, y, fo, ft, r, sg, v.bb, v.rr, es, d, kn ^ 1);
+            // (FP32: d is the increment of the other species' last system, and
+            // goes to its buffer hb; an increment of zero, of a field that has
+            // come to rest, changes nothing but that buffer once.  The slot's
+            // traffic bounds such steps: 4096 prior draws of 128^2, 8000 steps,
+            // rtol 1e-9: 2.90 s against 3.86 with the stores, at 1e-7 2.66
+            // against 3.86.)
+            const int hb = sp ? kn : kn ^ 1, zb = 1 << (2 * (1 - sp) + hb);
+            const bool advance = !kFp64 && (moved || !(zeroed & zb));
+            zeroed = moved ? zeroed & ~zb : zeroed | zb;
+            if (sp == 0 && advance)
+                residual<0, !kFp64>(x, y, fo, ft, r, sg, v.bb, v.rr, es, d, hb);
+            else if (sp == 0)
+                residual<0, false>(x, y, fo, ft, r, sg, v.bb, v.rr, es, d, hb);
+            else if (advance)
+                residual<1, !kFp64>(x, y, fo, ft, r, sg, v.bb, v.rr, es, d, hb);
             else
-                residual<1, !kFp64>(x, y, fo, ft, r, sg, v.bb, v.rr, es, d, kn);
+                residual<1, false>(x, y, fo, ft, r, sg, v.bb, v.rr, es, d, hb);
             int still = 0;
             v.it = 0;
             v.maxit = a.maxit;
             v.rtol2 = kFp64 ? fp64_rtol2(a.rtol2, y) : a.rtol2;
-            start(x, y, sp, kn, (quiet >> sp) & 1 ? 0 : np, r, sg, d, es, v, still);
+            const int npred = (quiet >> sp) & 1 ? 0 : np;
+            start(x, y, sp, kn, npred, r, sg, d, es, v, still);
             st = pcg(x, y, r, sg, d, v.rtol2 * v.bb, v);
             if constexpr (kFp64) {
                 if (st == 0)
                     st = refine(x, y, sp, fo, ft, 2 * (cur ^ 1) + sp, r, sg, d, v, kn);
             }
+            moved = uniform((int)(npred > 0 || v.it > 0));
             quiet = (quiet & ~(1 << sp)) | (still << sp);
             itu += sp == 0 ? v.it : 0;
             itv += sp == 1 ? v.it : 0;
