@@ -73,12 +73,14 @@ using S64 = Shape<64, 4, 16, 1>;
 using S128 = Shape<128, 8, 16, 1>;
 
 // Reduction slots (FP64, W each): the predictor's 8 sums of each species,
-// then |r|^2, r.z, p.q, the step size or true residual, and the misfit.  No
-// two consecutive reductions share one.
+// then |r|^2, r.z, p.q, the true residual of a refinement, the step size and
+// the misfit.  A sum is write, barrier, read, so a wave may write the next
+// sum while another still reads this one: no two consecutive reductions share
+// a slot (the step size follows a true residual or |r|^2 at once).
 template <int W>
 struct RedSlots {
-    static constexpr int gram = 0, rr = 16 * W, rz = 17 * W, pq = 18 * W, misc = 19 * W,
-                         misfit = 20 * W, total = 21 * W;
+    static constexpr int gram = 0, rr = 16 * W, rz = 17 * W, pq = 18 * W, truth = 19 * W,
+                         step = 20 * W, misfit = 21 * W, total = 22 * W;
 };
 
 // LDS of a workgroup.  qf / qt: Q and Q^T as matrix-core fragments (tile of
@@ -1035,7 +1037,7 @@ __device__ __forceinline__ int refine(X &x, const System &y, int sp, int fo, int
         correct(x, sp, fo, fn, first, d, hb);
         first = false;
         x.sync();
-        v.rr = x.sum1(true_residual(x, y, sp, fo, ft, fn, r), RedSlots<S::W>::misc);
+        v.rr = x.sum1(true_residual(x, y, sp, fo, ft, fn, r), RedSlots<S::W>::truth);
         if (!finite(v.rr))
             return kStNonfinite;
         if (!(v.rr > v.rtol2 * v.bb))
@@ -1179,7 +1181,7 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int c, const Grid
                 group_end();
             }
             const double thr = a.steady_tt * (double)N;
-            if (x.sum1(acc, RedSlots<S::W>::misc) < thr * thr)
+            if (x.sum1(acc, RedSlots<S::W>::step) < thr * thr)
                 break;
             if (n + 1 == a.n_steps)
                 st = kStNotSteady;  // the cap came first
