@@ -708,6 +708,7 @@ __device__ void finish_item(const SolveArgs &a, const GridDev &gd, int c, Arr &x
                 s += e * e;
             }
         }
+        __syncthreads();  // the step size's last readers are done (same slot)
         s = block_sum<NW>(s, red + Slots<NW>::misfit);
         if (threadIdx.x == 0)
             a.phi[c] = (st != 0 || !gd.y || !finite(s)) ? __builtin_inf() : s * gd.inv_2s2;
