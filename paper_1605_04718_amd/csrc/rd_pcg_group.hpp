@@ -4,7 +4,7 @@
 // Member m owns rows 64 m .. 64 m + 63 (eight waves of 8 rows, 4 columns per
 // lane) in a slot of its own.  The members exchange, through a per-group area
 // of global memory with agent-coherent loads and stores, the partial sums of
-// every reduction (tagged values, which are also the group's barrier, as in
+// every reduction (numbered words, which are also the group's barrier, as in
 // the plain-CG group above), the rows at the strips' edges, and twice per
 // application of the preconditioner an FP16 array: each member transforms its
 // 64 rows horizontally for all 256 modes, takes over 64 modes for both
@@ -36,13 +36,13 @@ struct GroupLds {
 };
 
 // Workspace of the groups: the item queue, every group's partial sums
-// [2][G][8] (zeroed before a launch), the tables Q and Q^T in fragment order,
+// [2][G][8] of two words (zeroed before a launch), the tables Q and Q^T in fragment order,
 // then per group the edge rows of the fields [4][G][2][N] f64, of the
 // increments [4][G][2][N] f32 and of z [G][2][N] f32, and the exchanged FP16
 // arrays [N][N] (modes of all rows; rows of all modes).
 struct GroupArea {
     static constexpr size_t N = S256::N, G = S256::G;
-    static constexpr size_t partial = 2 * G * 8 * sizeof(double);
+    static constexpr size_t partial = 2 * G * 8 * 2 * sizeof(uint64_t);
     static constexpr size_t table = N * N * sizeof(_Float16);
     static constexpr size_t xrows = 4 * G * 2 * N * sizeof(double);
     static constexpr size_t hrows = 4 * G * 2 * N * sizeof(float);
@@ -55,16 +55,6 @@ struct GroupArea {
     }
 };
 
-typedef unsigned long long u64;
-
-__device__ __forceinline__ void put64(void *p, u64 v)
-{
-    __hip_atomic_store((u64 *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ u64 get64(const void *p)
-{
-    return __hip_atomic_load((const u64 *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 // C columns of a row, coherently, at this lane's columns.
 template <int C, typename T>
 __device__ __forceinline__ void put_row(T *row, int col, const T (&v)[C])
@@ -97,7 +87,7 @@ struct GroupCtx {
     int m;                   // member
     unsigned seq;            // exchanges of this launch
     u64 wait_ticks;          // bound of one wait (100 MHz ticks)
-    double *part;            // partial sums of the group
+    u64 *part;               // partial sums of the group
     unsigned char *area;     // edge rows and exchanged arrays
     const _Float16 *qf, *qt;
 
@@ -105,7 +95,7 @@ struct GroupCtx {
         : s(lds), m(member), seq(0), wait_ticks(a.coop_wait_ticks)
     {
         unsigned char *ws = (unsigned char *)a.group_ws;
-        part = (double *)(ws + 256 + (size_t)group * GroupArea::partial);
+        part = (u64 *)(ws + 256 + (size_t)group * GroupArea::partial);
         unsigned char *tab = ws + GroupArea::head(a.group_cap);
         qf = (const _Float16 *)tab;
         qt = (const _Float16 *)(tab + GroupArea::table);
@@ -156,50 +146,28 @@ struct GroupCtx {
         __builtin_amdgcn_s_waitcnt(0);
     }
     // Sums over the members of M values that every thread of the member holds,
-    // in member order (the same bits in every member).  A member publishes
-    // all eight of its slots each time (zero past M), so that a stale tag is
-    // always two exchanges old.  The tags' bits are cleared before the values
-    // are added: an item's result does not depend on how many exchanges its
-    // group made before.  Bounded: a member that waits too long raises
-    // fail and never waits again, so every exchange ends.
+    // in member order (the same bits in every member).  A value travels as two
+    // words, a half of it and the exchange's number each, so that the word is
+    // its own arrival flag and the sum loses no bits; with numbers of 32 bits,
+    // zeroed before a launch, no stale word can match.  Bounded: a member that
+    // waits too long raises fail and never waits again, so every exchange ends.
     template <int M>
     __device__ void exchange(double (&v)[M])
     {
-        static_assert(M <= 8, "slots");
+        static_assert(M <= 8 && S::G * 2 * M <= kWave, "one lane per word");
         seq += 1;
-        const unsigned tag = seq & 0xFFu;
-        double *buf = part + (size_t)(seq & 1u) * S::G * 8;
+        u64 *buf = part + (size_t)(seq & 1u) * S::G * 16;
         const int t = threadIdx.x;
-        if (t < 8) {
-            double mine = 0.0;
-#pragma unroll
-            for (int q = 0; q < M; ++q)
-                if (t == q)
-                    mine = v[q];
-            const double pub = with_tag(mine, tag);
-            coop_store(buf + lane_off(m * 8 + t), pub);
-            if (t < M)
-                s.gather[m * M + t] = with_tag(mine, 0u);
+        unsigned *got = (unsigned *)s.gather;  // [member][value][half]
+        if (t < 2 * M) {
+            const unsigned mine = half_of(v, t);
+            put64(buf + lane_off(m * 16 + t), (u64)mine << 32 | seq);
+            got[m * 2 * M + t] = mine;
         }
         asm volatile("" ::: "memory");  // the store is issued before any poll
-        if (t < S::G * M && t / M != m) {
-            const int mm = t / M, j = t % M;
-            double got = 0.0;
-            if (!s.fail) {
-                got = coop_load(buf + lane_off(mm * 8 + j));
-                if (tag_of(got) != tag) {
-                    const u64 t0 = __builtin_amdgcn_s_memrealtime();
-                    do {
-                        __builtin_amdgcn_s_sleep(1);
-                        got = coop_load(buf + lane_off(mm * 8 + j));
-                        if (__builtin_amdgcn_s_memrealtime() - t0 > wait_ticks) {
-                            s.fail = 1;
-                            break;
-                        }
-                    } while (tag_of(got) != tag);
-                }
-            }
-            s.gather[t] = with_tag(got, 0u);
+        if (t < S::G * 2 * M && t / (2 * M) != m) {
+            const int mm = t / (2 * M), j = t % (2 * M);
+            got[t] = await(buf + lane_off(mm * 16 + j), seq, wait_ticks, &s.fail);
         }
         __syncthreads();
 #pragma unroll

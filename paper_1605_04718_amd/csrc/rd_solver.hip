@@ -921,9 +921,9 @@ __global__ void k_note_cost(int n, const int *need, const int *iters, int *cost)
 // keeps it in registers, p in LDS (16 cells per thread, 1024 threads); the 5-point stencil needs the neighbouring members' edge
 // rows, and CG's dot products need the group's sums.  Both go through a
 // per-group area of global memory with agent-coherent (sc1) loads and
-// stores.  A group exchange publishes each member's partial sums tagged
+// stores.  A group exchange publishes each member's partial sums marked
 // with the exchange's sequence number and polls the other members' slots
-// until their tags match; it doubles as the group barrier, since a member
+// until their numbers match; it doubles as the group barrier, since a member
 // publishes only after its own edge-row stores have completed.  No cache
 // flush or invalidate is involved, so other workgroups' cached data is left
 // alone.  The members of a group get workgroup ids that are congruent
@@ -943,10 +943,10 @@ constexpr int kCoopR = kCoopStrip * kCoopN / kCoopThreads;  // 16 cells per thre
 // wait, it only bounds the damage of a member that can never arrive.
 
 struct CoopArea {
-    // header: the item queue; then per group: partial sums [2][G][4]
-    // doubles, then edge rows [4 fields][G][2][N]
+    // header: the item queue; then per group: partial sums [2][G][4] of two
+    // words, then edge rows [4 fields][G][2][N]
     static constexpr size_t header_bytes = 256;
-    static constexpr size_t partial_bytes = 2 * kCoopG * 4 * sizeof(double);
+    static constexpr size_t partial_bytes = 2 * kCoopG * 4 * 2 * sizeof(uint64_t);
     static constexpr size_t group_bytes =
         partial_bytes + (size_t)4 * kCoopG * 2 * kCoopN * sizeof(float);
 };
@@ -966,9 +966,9 @@ struct CoopCtx {
     double *gather;       // LDS [G * 4]
     unsigned long long wait_ticks;  // bound of one wait
 
-    __device__ double *partial(unsigned k) const
+    __device__ unsigned long long *partial(unsigned k) const
     {
-        return (double *)base + (size_t)(k & 1u) * kCoopG * 4;
+        return (unsigned long long *)base + (size_t)(k & 1u) * kCoopG * 8;
     }
     __device__ float *halo_row(int field, int member, int side) const
     {
@@ -994,88 +994,81 @@ __device__ __forceinline__ float coop_load(const float *p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void coop_store(double *p, double v)
+typedef unsigned long long u64;
+
+__device__ __forceinline__ void put64(void *p, u64 v)
 {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store((u64 *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ double coop_load(const double *p)
+__device__ __forceinline__ u64 get64(const void *p)
 {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_load((const u64 *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// A published value carries the exchange's sequence number in its 8 lowest
-// mantissa bits, so the value is its own arrival flag: one coherent store
-// and one poll per member, no counter.  The change is below 2^-44 relative,
-// far under the rounding error of the FP64 sums themselves, and every
-// member sums the same tagged values in the same order.  Exchanges are
-// double buffered by sequence parity, and every exchange rewrites all four
-// slots of its member (unused ones carry zero), so a slot's stale tag is
-// always exactly two behind.  (Were only the M slots in use rewritten, a
-// slot that a long run of one-value exchanges leaves alone would hold the
-// tag of an exchange 256 k sequence numbers back, which the 8-bit tag
-// cannot tell from the present one: the poll would take the old value, and
-// the exchange would stop being a barrier.)
-__device__ __forceinline__ double with_tag(double v, unsigned tag)
+// A value that a group exchanges is published as two words, half of its bits
+// and the exchange's number each: a word is its own arrival flag (one coherent
+// store and one poll, no counter), and the value loses no bits.  Exchanges are
+// double buffered by the number's parity; the area is zeroed before a launch
+// and the numbers count from 1, so no stale word can match.
+
+// Half t % 2 (0: low) of value t / 2.
+template <int M>
+__device__ __forceinline__ unsigned half_of(const double (&v)[M], int t)
 {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    return __longlong_as_double((long long)((b & ~0xFFull) | (tag & 0xFFu)));
+    u64 mine = 0;
+#pragma unroll
+    for (int q = 0; q < M; ++q)
+        if (t / 2 == q)
+            mine = (u64)__double_as_longlong(v[q]);
+    return (unsigned)(t & 1 ? mine >> 32 : mine);
 }
-__device__ __forceinline__ unsigned tag_of(double v)
+
+// The half published at p with number seq.  Raises *fail after wait_ticks, and
+// does not wait when it is up.
+__device__ __forceinline__ unsigned await(const u64 *p, unsigned seq, u64 wait_ticks, int *fail)
 {
-    return (unsigned)((unsigned long long)__double_as_longlong(v) & 0xFFu);
+    if (*fail)
+        return 0;
+    u64 w = get64(p);
+    if ((unsigned)w != seq) {
+        const u64 t0 = __builtin_amdgcn_s_memrealtime();
+        do {
+            __builtin_amdgcn_s_sleep(1);
+            w = get64(p);
+            if (__builtin_amdgcn_s_memrealtime() - t0 > wait_ticks) {
+                *fail = 1;
+                break;
+            }
+        } while ((unsigned)w != seq);
+    }
+    return (unsigned)(w >> 32);
 }
 
 // Group exchange of M values that every thread of the member holds: on
 // return v holds the sums over the members, in member order (the same in
-// every member).  Also a group barrier: every coherent store that a thread
-// of any member issued before the exchange is visible after it.  Bounded:
-// after x.wait_ticks the member gives up and raises *fail, and a member
-// that has failed no longer waits, so every exchange ends.
+// every member).  Bounded: after x.wait_ticks the member gives up and raises
+// *fail, and a member that has failed no longer waits, so every exchange ends.
 template <int M>
-__device__ void coop_exchange(double (&v)[M], CoopCtx &x)
+__device__ __forceinline__ void coop_trade(double (&v)[M], CoopCtx &x)
 {
-    // this thread's coherent stores are complete before the value is published
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
+    static_assert(M <= 4, "slots");
     x.seq += 1;
-    const unsigned tag = x.seq & 0xFFu;
-    double *buf = x.partial(x.seq);
+    u64 *buf = x.partial(x.seq);
     const int t = threadIdx.x;
+    unsigned *got = (unsigned *)x.gather;  // [member][value][half]
     // The store and the polls are separate blocks, store first: as the
     // two sides of one branch they could run in either order within the
     // wave, and a wave that polls before it stores waits for members that
     // do the same.
-    if (t < 4) {  // this member's four slots, value t (zero past M)
-        double mine = 0.0;
-#pragma unroll
-        for (int q = 0; q < M; ++q)
-            if (t == q)
-                mine = v[q];
-        const double pub = with_tag(mine, tag);
-        coop_store(buf + lane_off(x.m * 4 + t), pub);
-        if (t < M)
-            x.gather[x.m * M + t] = pub;
+    if (t < 2 * M) {
+        const unsigned mine = half_of(v, t);
+        put64(buf + lane_off(x.m * 8 + t), (u64)mine << 32 | x.seq);
+        got[x.m * 2 * M + t] = mine;
     }
     asm volatile("" ::: "memory");
-    if (t < kCoopG * M && t / M != x.m) {
-        const int mm = t / M, j = t % M;  // lane t: value j of member mm
-        double got = 0.0;
-        if (!*x.fail) {
-            got = coop_load(buf + lane_off(mm * 4 + j));
-            if (tag_of(got) != tag) {
-                const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
-                do {
-                    __builtin_amdgcn_s_sleep(1);
-                    got = coop_load(buf + lane_off(mm * 4 + j));
-                    if (__builtin_amdgcn_s_memrealtime() - t0 > x.wait_ticks) {
-                        *x.fail = 1;
-                        break;
-                    }
-                } while (tag_of(got) != tag);
-            }
-        }
-        x.gather[t] = got;
+    if (t < kCoopG * 2 * M && t / (2 * M) != x.m) {
+        const int mm = t / (2 * M), j = t % (2 * M);
+        got[t] = await(buf + lane_off(mm * 8 + j), x.seq, x.wait_ticks, x.fail);
     }
     __syncthreads();
 #pragma unroll
@@ -1088,6 +1081,18 @@ __device__ void coop_exchange(double (&v)[M], CoopCtx &x)
     }
 }
 
+// The same, and a group barrier: every coherent store that a thread of any
+// member issued before the exchange is visible after it.
+template <int M>
+__device__ void coop_exchange(double (&v)[M], CoopCtx &x)
+{
+    // this thread's coherent stores are complete before the value is published
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    coop_trade(v, x);
+}
+
 // Group barrier (an exchange of nothing).
 __device__ __forceinline__ void coop_sync(CoopCtx &x)
 {
@@ -1095,12 +1100,10 @@ __device__ __forceinline__ void coop_sync(CoopCtx &x)
     coop_exchange<1>(z, x);
 }
 
-// Sums of M per-thread values over the group's threads.
+// Sums of M per-thread values over the group's threads, and a group barrier.
 template <int NW, int M>
 __device__ void coop_sum(double (&v)[M], double *red, CoopCtx &x)
 {
-    // as block_sum_n followed by coop_exchange, with one workgroup barrier
-    // fewer: the lanes that publish form this member's sums themselves
 #pragma unroll
     for (int m = 0; m < M; ++m)
         v[m] = wave_sum_last_lane(v[m]);
@@ -1114,51 +1117,8 @@ __device__ void coop_sum(double (&v)[M], double *red, CoopCtx &x)
             red[m * NW + t / kWave] = v[m];
     }
     __syncthreads();
-    double own[M];
-    slots_sum<NW>(own, red);  // this member's sums (wave-uniform)
-    x.seq += 1;
-    const unsigned tag = x.seq & 0xFFu;
-    double *buf = x.partial(x.seq);
-    if (t < 4) {  // lanes 0..3 publish this member's four slots (zero past M)
-        double sum = 0.0;
-#pragma unroll
-        for (int q = 0; q < M; ++q)
-            if (t == q)
-                sum = own[q];
-        const double pub = with_tag(sum, tag);
-        coop_store(buf + lane_off(x.m * 4 + t), pub);
-        if (t < M)
-            x.gather[x.m * M + t] = pub;
-    }
-    asm volatile("" ::: "memory");  // the store is issued before any poll
-    if (t < kCoopG * M && t / M != x.m) {
-        const int mm = t / M, j = t % M;  // lane t: value j of member mm
-        double got = 0.0;
-        if (!*x.fail) {
-            got = coop_load(buf + lane_off(mm * 4 + j));
-            if (tag_of(got) != tag) {
-                const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
-                do {
-                    __builtin_amdgcn_s_sleep(1);
-                    got = coop_load(buf + lane_off(mm * 4 + j));
-                    if (__builtin_amdgcn_s_memrealtime() - t0 > x.wait_ticks) {
-                        *x.fail = 1;
-                        break;
-                    }
-                } while (tag_of(got) != tag);
-            }
-        }
-        x.gather[t] = got;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < M; ++j) {
-        double sum = 0.0;
-#pragma unroll
-        for (int mm = 0; mm < kCoopG; ++mm)
-            sum += x.gather[mm * M + j];
-        v[j] = uniform(sum);
-    }
+    slots_sum<NW>(v, red);  // this member's sums (wave-uniform)
+    coop_trade(v, x);
 }
 
 // Thread layout of a member: thread t owns column i = t % N, local rows
@@ -1789,7 +1749,7 @@ hipError_t launch_solve_coop(const SolveArgs &a, int wgs, hipStream_t s)
     if (!a.coop || !a.gws || grid < 32 || grid / kCoopG > a.coop_groups || grid > a.gws_slots ||
         a.gws_stride < (size_t)4 * kCoopStrip * kCoopN * sizeof(float))
         return hipErrorInvalidValue;
-    // the queue starts at 0, and stale tags of an earlier launch must not
+    // the queue starts at 0, and exchange numbers of an earlier launch must not
     // match this launch's
     hipError_t e = launch_fill_u32((unsigned *)a.coop, 0u,
                                    (int)(coop_workspace_bytes(grid / kCoopG) / sizeof(unsigned)), s);
@@ -2028,7 +1988,7 @@ hipError_t launch_solve_group(int precision, SolveArgs a, int wgs, bool mixed, h
     if (a.coop_wgs > 0) {
         if (!a.group_ws || a.coop_wgs / S256::G > a.group_cap)
             return hipErrorInvalidValue;
-        // the queue starts at 0, and stale tags of an earlier launch must not
+        // the queue starts at 0, and exchange numbers of an earlier launch must not
         // match this launch's
         const size_t head = GroupArea::head(a.coop_wgs / S256::G);
         const hipError_t e = launch_fill_u32((unsigned *)a.group_ws, 0u, (int)(head / 4), s);
