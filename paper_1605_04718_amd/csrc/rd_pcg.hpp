@@ -1222,8 +1222,16 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int c, const Grid
         }
         group_end();
     }
-    if (a.phi) {
+    // A group's last exchange, with or without a misfit: any member that gave
+    // up a wait before it (and may have written wrong rows) is silent in it, so
+    // that the leader gives up too and reports the item failed.
+    if (a.phi)
         sum = x.sum1(sum, RedSlots<S::W>::misfit);
+    else if (S::G > 1)
+        x.sync();
+    if (x.failed())
+        st = kStGroupTimeout;
+    if (a.phi) {
         if (x.leader())
             a.phi[c] = (st != 0 || !gd.y || !finite(sum)) ? __builtin_inf() : sum * gd.inv_2s2;
     }

@@ -150,7 +150,10 @@ struct GroupCtx {
     // words, a half of it and the exchange's number each, so that the word is
     // its own arrival flag and the sum loses no bits; with numbers of 32 bits,
     // zeroed before a launch, no stale word can match.  Bounded: a member that
-    // waits too long raises fail and never waits again, so every exchange ends.
+    // waits too long raises fail, and neither waits nor publishes again, so
+    // every exchange ends, and the other members take none of its later values
+    // for sums: they give up in turn at their next exchange, before the item is
+    // reported.
     template <int M>
     __device__ void exchange(double (&v)[M])
     {
@@ -161,7 +164,8 @@ struct GroupCtx {
         unsigned *got = (unsigned *)s.gather;  // [member][value][half]
         if (t < 2 * M) {
             const unsigned mine = half_of(v, t);
-            put64(buf + lane_off(m * 16 + t), (u64)mine << 32 | seq);
+            if (!s.fail)
+                put64(buf + lane_off(m * 16 + t), (u64)mine << 32 | seq);
             got[m * 2 * M + t] = mine;
         }
         asm volatile("" ::: "memory");  // the store is issued before any poll

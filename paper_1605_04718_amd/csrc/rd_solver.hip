@@ -1047,7 +1047,9 @@ __device__ __forceinline__ unsigned await(const u64 *p, unsigned seq, u64 wait_t
 // Group exchange of M values that every thread of the member holds: on
 // return v holds the sums over the members, in member order (the same in
 // every member).  Bounded: after x.wait_ticks the member gives up and raises
-// *fail, and a member that has failed no longer waits, so every exchange ends.
+// *fail, and a member that has failed neither waits nor publishes again, so
+// every exchange ends and the other members give up in turn at their next one,
+// before the item is reported.
 template <int M>
 __device__ __forceinline__ void coop_trade(double (&v)[M], CoopCtx &x)
 {
@@ -1062,7 +1064,8 @@ __device__ __forceinline__ void coop_trade(double (&v)[M], CoopCtx &x)
     // do the same.
     if (t < 2 * M) {
         const unsigned mine = half_of(v, t);
-        put64(buf + lane_off(x.m * 8 + t), (u64)mine << 32 | x.seq);
+        if (!*x.fail)
+            put64(buf + lane_off(x.m * 8 + t), (u64)mine << 32 | x.seq);
         got[x.m * 2 * M + t] = mine;
     }
     asm volatile("" ::: "memory");
@@ -1601,8 +1604,14 @@ __device__ void solve_item_coop(const SolveArgs &a, int c, const GridDev &gd, fl
         }
         double v1[1] = {sum};
         coop_sum<NW>(v1, red, x);
+        if (*x.fail)
+            st = kStGroupTimeout;
         if (threadIdx.x == 0 && x.m == 0)
             a.phi[c] = (st != 0 || !gd.y || !finite(v1[0])) ? __builtin_inf() : v1[0] * gd.inv_2s2;
+    } else {
+        coop_sync(x);  // (a member that gave up is silent: the leader gives up too)
+        if (*x.fail)
+            st = kStGroupTimeout;
     }
     if (threadIdx.x == 0 && x.m == 0) {
         a.status[c] = st;
