@@ -799,6 +799,14 @@ __device__ __forceinline__ int pcg(X &x, const System &y, float (&r)[X::Sh::R],
     constexpr int C = S::C, R = S::R, N = S::N;
     const float cf = uniform((float)y.c);
     const float cs = uniform((float)(y.c / v.sbar));
+    // The stiffest mode leaves stage 2 divided by 1 + 8 cs.  Where that takes
+    // it below the normal FP16 numbers (2^-14), the stages run scaled up by
+    // 2^kHead, which puts the largest value, N times the r.m.s. one, just below
+    // the largest FP16, and the iteration converges up to 8 c dt = 3e7, as far
+    // as plain CG in FP32 does; without it, from 3e7 on (at 1e7 in 21 to 90
+    // iterations) it does not.
+    constexpr int kHead = N == 32 ? 10 : N == 64 ? 9 : N == 128 ? 8 : 7;
+    constexpr int kStiff = 0x45000000;  // the bits of 2048.0f
     float p[R], q[R], ps[C], pn[C];
     double rz_old = 1.0;
     int st = (finite(v.bb) && finite(v.rr)) ? 0 : kStNonfinite;
@@ -813,9 +821,10 @@ __device__ __forceinline__ int pcg(X &x, const System &y, float (&r)[X::Sh::R],
             break;
         }
         // power of two near the r.m.s. residual (the FP16 stages see values
-        // near 1; one coefficient can hold all of |r|, at most N)
+        // near 1; one coefficient can hold all of |r|, at most N), less head
         int ex = uniform(__builtin_amdgcn_frexp_exp(v.rr * (1.0 / ((double)N * N)))) >> 1;
-        ex = ex < -100 ? -100 : ex > 100 ? 100 : ex;
+        ex = (ex < -100 ? -100 : ex > 100 ? 100 : ex) -
+             (__float_as_int(cs) > kStiff ? kHead : 0);
         const float scale = ldexpf(1.0f, -ex);
         const float out = uniform((float)(ldexp(1.0, ex) / v.sbar));
         if (v.maxit >= kPlainCap) {

@@ -1859,7 +1859,7 @@ static void spectral(int n, int precision, F &&f)
     if (n == 32)
         f(k_solve_pcg<S32, false, 4>, S32::T);
     else if (n == 64)
-        precision ? f(k_solve_pcg<S64, true, 2>, S64::T) : f(k_solve_pcg<S64, false, 3>, S64::T);
+        precision ? f(k_solve_pcg<S64, true, 3>, S64::T) : f(k_solve_pcg<S64, false, 3>, S64::T);
     else
         precision ? f(k_solve_pcg<S128, true, 2>, S128::T)
                   : f(k_solve_pcg<S128, false, 2>, S128::T);
