@@ -338,7 +338,10 @@ int32_t enqueue_solve(rd_problem *p, int n, const double *theta, const int *grid
     // (a cooperative tile sizes its grid from the item count itself)
     if (wgs > n && !tile_coop(nn, p->desc.precision, t.cpt))
         wgs = n;
-    HIP_TRY(launch_fill_u32(a.queue, 0u, mixed ? 3 : 1, s));
+    // queue heads: the launch's (a mixed batch's three), then those of the
+    // FP64 items that are left to plain CG, by size, and their number
+    HIP_TRY(launch_fill_u32(a.queue, 0u, 7, s));
+    a.redo_count = a.queue + 6;
     if (mixed) {
         HIP_TRY(launch_class_order(grid_id, n, p->desc.n_grids, p->rank, p->order_ws, s));
         a.order = p->order_ws;
@@ -349,6 +352,7 @@ int32_t enqueue_solve(rd_problem *p, int n, const double *theta, const int *grid
     hipEvent_t e0 = nullptr;
     if (!ws)  // (event creation may allocate: an external workspace is never timed)
         HIP_TRY(record_solve_start(p, s, &e0));
+    unsigned *const heads = a.queue;
     if (!mixed) {
         HIP_TRY(launch_solve(nn, p->desc.precision, t, a, wgs, s));
     } else {
@@ -358,7 +362,6 @@ int32_t enqueue_solve(rd_problem *p, int n, const double *theta, const int *grid
         // smaller and share a CU.  Each launch has a queue head of its own and
         // passes over the other sizes.
         const int prec = p->desc.precision;
-        unsigned *queue = a.queue;
         if (p->has_n[0] || p->has_n[1]) {
             int big = std::min(p->n_cu, p->gws_slots) / 32 * 32;
             big = std::min(big, (n * kCoopG + 31) / 32 * 32);
@@ -369,10 +372,18 @@ int32_t enqueue_solve(rd_problem *p, int n, const double *theta, const int *grid
         for (int k = 0; k < 2; ++k) {
             if (!p->has_n[2 + k])
                 continue;
-            a.queue = queue + 1 + k;
+            a.queue = heads + 1 + k;
             const int most = std::min(p->n_cu * p->class_wpc[k], p->gws_slots);
             HIP_TRY(launch_solve_class(k == 0 ? 64 : 32, prec, a, std::min(most, n), s));
         }
+    }
+    for (int k = 0; k < 3; ++k) {
+        const int m = 256 >> k;
+        const bool refined = p->desc.precision == RD_PRECISION_FP64 &&
+                             (mixed ? p->has_n[k] : nn == m && tile_refined(nn, 1, t.cpt));
+        a.queue = heads + 3 + k;
+        if (refined)
+            HIP_TRY(launch_solve_plain64(m, a, false, s));
     }
     HIP_TRY(record_solve_end(p, s, e0));
     return RD_OK;

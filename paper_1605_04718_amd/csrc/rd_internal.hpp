@@ -12,7 +12,9 @@ enum : int {
     kStOutOfPrior = 8,
     kStBadGrid = 16,
     kStNotSteady = 32,
-    kStGroupTimeout = 64
+    kStGroupTimeout = 64,
+    // (inside a call) to be solved again by FP64 plain CG
+    kStRedo = 1 << 30
 };
 
 // One grid class as the kernels see it (device memory).
@@ -63,6 +65,8 @@ struct SolveArgs {
     void *group_ws;          // workspace of the 256^2 groups, or null
     int group_cap;           // groups it holds
     int coop_wgs;            // leading workgroups of the launch that form groups
+    unsigned *redo_count;    // items marked kStRedo so far
+    bool redo_only;          // streamed kernel: only the items marked kStRedo
     unsigned long long coop_wait_ticks;   // bound of a group wait (100 MHz ticks)
     unsigned long long coop_stall_ticks;  // test hook: member 1 of every group
                                           // sleeps this long first (0: off)
@@ -83,6 +87,11 @@ constexpr int kGroupCpt = 32;  // its tile (cells per thread)
 size_t group_workspace_bytes(int groups);
 hipError_t launch_group_tables(void *ws, int groups, hipStream_t s);
 hipError_t launch_solve_group(int precision, SolveArgs a, int wgs, bool mixed, hipStream_t s);
+// FP64 plain CG with every array in global memory, for the items of size n that
+// the preconditioned FP64 solve leaves to it (all: every item).
+hipError_t launch_solve_plain64(int n, SolveArgs a, bool all, hipStream_t s);
+// FP64 tile of the preconditioned solve.
+bool tile_refined(int n, int precision, int cpt);
 // The 32^2 or 64^2 items of a class-ordered batch.
 hipError_t launch_solve_class(int n, int precision, const SolveArgs &a, int wgs, hipStream_t s);
 

@@ -788,11 +788,11 @@ __device__ __forceinline__ void start(X &x, const System &y, int sp, int kn, int
 constexpr int kPlainCap = 16;
 
 // Preconditioned CG: d += A^-1 r until |r|^2 <= stop2 (r is updated
-// recursively).  Returns RD status bits.
+// recursively).  Returns RD status bits; st, if it is set, before any iteration.
 template <class X>
 __device__ __forceinline__ int pcg(X &x, const System &y, float (&r)[X::Sh::R],
                                    const float (&sg)[X::Sh::R], float (&d)[X::Sh::R],
-                                   double stop2, Scalars &v)
+                                   double stop2, Scalars &v, int st = 0)
 {
     using S = typename X::Sh;
     using RS = RedSlots<S::W>;
@@ -809,7 +809,7 @@ __device__ __forceinline__ int pcg(X &x, const System &y, float (&r)[X::Sh::R],
     constexpr int kStiff = 0x45000000;  // the bits of 2048.0f
     float p[R], q[R], ps[C], pn[C];
     double rz_old = 1.0;
-    int st = (finite(v.bb) && finite(v.rr)) ? 0 : kStNonfinite;
+    st = (finite(v.bb) && finite(v.rr)) || st ? st : kStNonfinite;
     bool first = true;
     while (st == 0 && v.rr > stop2) {
         if (x.failed()) {
@@ -909,6 +909,22 @@ __device__ __forceinline__ int pcg(X &x, const System &y, float (&r)[X::Sh::R],
     if (x.failed())
         st = kStGroupTimeout;
     return st;
+}
+
+// FP64 problems: a system that the FP32 corrections cannot be relied on for,
+// because the right-hand side's size leaves their range (with it the residuals,
+// 1e-15 as large, and the products of the fields in sigma), or because it is so
+// stiff that the preconditioner helps little and the FP32 operator's rounding
+// reaches the smooth part.  Such items are solved again from the start by plain
+// CG in FP64.  Measured at rtol 1e-12, iterations of two steps of 64 x 64, 128 x
+// 128 and 256 x 256 from rough fields, here | plain: 8 c dt = 1e6 57, 47, 57 |
+// 1100 to 4000; 1e7 235, 122, 157; 3e7 623, 432, 279; 1e8 more than 4000.
+template <class S>
+__device__ __forceinline__ bool out_of_range(const System &y, const Scalars &v)
+{
+    constexpr double cells = (double)S::N * S::N;
+    return finite(v.bb) && v.bb > 0.0 &&
+           (v.bb < 0x1p-80 * cells || v.bb > 0x1p80 * cells || 8.0 * y.c > 0x1p24 * v.sbar);
 }
 
 // FP64 problems.  Adds the correction d to the new field fn (kFirst: to the
@@ -1145,7 +1161,7 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int c, const Grid
             v.rtol2 = kFp64 ? fp64_rtol2(a.rtol2, y) : fp32_rtol2(a.rtol2, sp);
             const int npred = (quiet >> sp) & 1 ? 0 : np;
             start(x, y, sp, kn, npred, r, sg, d, es, v, still);
-            st = pcg(x, y, r, sg, d, v.rtol2 * v.bb, v);
+            st = pcg(x, y, r, sg, d, v.rtol2 * v.bb, v, kFp64 && out_of_range<S>(y, v) ? kStRedo : 0);
             if constexpr (kFp64) {
                 if (st == 0)
                     st = refine(x, y, sp, fo, ft, 2 * (cur ^ 1) + sp, r, sg, d, v, kn);
@@ -1246,6 +1262,8 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int c, const Grid
     }
     if (x.leader()) {
         a.status[c] = st;
+        if (kFp64 && st == kStRedo)
+            atomicAdd(a.redo_count, 1u);
         if (a.steps_out)
             a.steps_out[c] = steps;
         if (a.iters) {

@@ -789,12 +789,15 @@ __global__ __launch_bounds__(N *N / R) void k_solve_streamed(SolveArgs a)
     __shared__ double red[Slots<NW>::total];
     __shared__ int s_item;
     Real *slot = (Real *)((char *)a.gws + (size_t)blockIdx.x * a.gws_stride);
+    if (a.redo_only && uniform((int)*a.redo_count) == 0)
+        return;
     for (int item = next_item(a.queue, &s_item); item < a.n_items;
          item = next_item(a.queue, &s_item)) {
         const int c = uniform(a.order ? a.order[item] : item);
-        if (!a.need || uniform(a.need[c])) {
+        if ((!a.need || uniform(a.need[c])) &&
+            (!a.redo_only || uniform(a.status[c]) == kStRedo)) {
             const int gid = item_grid(a, c);
-            if (gid >= 0)
+            if (gid >= 0 && uniform(a.grids[gid].n) == N)
                 solve_item_streamed<N, R, Real>(a, c, a.grids[gid], red, slot);
         }
     }
@@ -2011,6 +2014,24 @@ hipError_t launch_solve_group(int precision, SolveArgs a, int wgs, bool mixed, h
     return hipGetLastError();
 }
 
+hipError_t launch_solve_plain64(int n, SolveArgs a, bool all, hipStream_t s)
+{
+    // the slots of the preconditioned solve, cut anew: 12 arrays (SlotLayout)
+    const size_t room = (size_t)a.gws_slots * a.gws_stride;
+    a.gws_stride = (size_t)12 * n * n * sizeof(double);
+    a.redo_only = !all;
+    const int wgs = (int)std::min<size_t>(std::min(a.n_items, a.gws_slots), room / a.gws_stride);
+    if (!a.gws || wgs < 1)
+        return hipErrorInvalidValue;
+    if (n == 64)
+        return go_streamed<64, 16, double>(a, wgs, s);
+    if (n == 128)
+        return go_streamed<128, 32, double>(a, wgs, s);
+    if (n == 256)
+        return go_streamed<256, 128, double>(a, wgs, s);
+    return hipErrorInvalidValue;
+}
+
 // The items of one small class size (32 or 64) of a class-ordered batch.
 hipError_t launch_solve_class(int n, int precision, const SolveArgs &a, int wgs, hipStream_t s)
 {
@@ -2028,6 +2049,12 @@ hipError_t launch_solve_class(int n, int precision, const SolveArgs &a, int wgs,
 bool tile_streamed(int n, int precision, int cpt)
 {
     return tile_kind(n, precision, cpt) == kStreamed;
+}
+
+bool tile_refined(int n, int precision, int cpt)
+{
+    const Kind k = tile_kind(n, precision, cpt);
+    return precision != 0 && (k == kSpectral || k == kSpectralGroup);
 }
 
 bool tile_coop(int n, int precision, int cpt)
