@@ -664,7 +664,7 @@ __device__ __forceinline__ void load_strip(const X &x, const float *a, float (&v
 
 // The scalars of one solve that its passes share.
 struct Scalars {
-    double bb, rr, sbar, rtol2;
+    double bb, rr, sbar, rtol2, floor2;
     int maxit, it;
 };
 
@@ -1026,10 +1026,14 @@ __device__ __forceinline__ double true_residual(const X &x, const System &y, int
 // stands for a larger error of the field (A is 1/dt on the smooth part, up to
 // 8 c on the rough one): a twentieth of the caller's tolerance gives the
 // accuracy that plain CG had at it, but not below the rounding of the
-// evaluated residual.
-__device__ __forceinline__ double fp64_rtol2(double rtol2, const System &y)
+// evaluated residual (squared, of |b|: a field of the size of the present one,
+// rounded to FP64, through the operator, 2^-53 (1 + 8 c dt) / 2, a few times).
+__device__ __forceinline__ double fp64_floor2(double c_dt)
 {
-    const double floor2 = 1e-30 * (8.0 + 8.0 * y.c / y.inv_dt) * (8.0 + 8.0 * y.c / y.inv_dt);
+    return 6.4e-29 * (1.0 + c_dt) * (1.0 + c_dt);
+}
+__device__ __forceinline__ double fp64_rtol2(double rtol2, double floor2)
+{
     return fmax(0.0025 * rtol2, fmin(rtol2, floor2));
 }
 
@@ -1046,9 +1050,11 @@ __device__ __forceinline__ double fp32_rtol2(double rtol2, int sp)
 }
 
 // Corrections of an FP64 system after its first solve: refined until the
-// evaluated residual meets the tolerance.  A residual that has stopped
-// falling although every correction converged is at the rounding level of
-// its own evaluation and is accepted.
+// evaluated residual meets the tolerance.  One that has stopped falling although
+// every correction converged is accepted only at the rounding of its evaluation
+// (a tolerance below that); elsewhere the item goes to plain CG (an operator
+// within 1e-8 of a singular one, whose solution is so much larger than the
+// present field that it sets the rounding).
 template <class X>
 __device__ __forceinline__ int refine(X &x, const System &y, int sp, int fo, int ft, int fn,
                                       float (&r)[X::Sh::R], const float (&sg)[X::Sh::R],
@@ -1069,7 +1075,7 @@ __device__ __forceinline__ int refine(X &x, const System &y, int sp, int fo, int
             return 0;
         stalled = v.rr > 0.25 * best ? stalled + 1 : 0;
         if (stalled >= 3)
-            return 0;
+            return v.rr > v.floor2 * v.bb ? kStRedo : 0;
         best = v.rr < best ? v.rr : best;
 #pragma unroll
         for (int i = 0; i < S::R; ++i)
@@ -1158,7 +1164,8 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int c, const Grid
             int still = 0;
             v.it = 0;
             v.maxit = a.maxit;
-            v.rtol2 = kFp64 ? fp64_rtol2(a.rtol2, y) : fp32_rtol2(a.rtol2, sp);
+            v.floor2 = kFp64 ? uniform(fp64_floor2(y.c * a.dt)) : 0.0;
+            v.rtol2 = kFp64 ? uniform(fp64_rtol2(a.rtol2, v.floor2)) : fp32_rtol2(a.rtol2, sp);
             const int npred = (quiet >> sp) & 1 ? 0 : np;
             start(x, y, sp, kn, npred, r, sg, d, es, v, still);
             st = pcg(x, y, r, sg, d, v.rtol2 * v.bb, v, kFp64 && out_of_range<S>(y, v) ? kStRedo : 0);
