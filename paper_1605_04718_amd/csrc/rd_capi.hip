@@ -353,8 +353,16 @@ int32_t enqueue_solve(rd_problem *p, int n, const double *theta, const int *grid
     if (!ws)  // (event creation may allocate: an external workspace is never timed)
         HIP_TRY(record_solve_start(p, s, &e0));
     unsigned *const heads = a.queue;
+    // FP64 sizes solved by FP32 corrections: plain CG takes what those leave,
+    // and everything under a small iteration cap
+    const bool fp64 = p->desc.precision == RD_PRECISION_FP64;
+    const bool plain = fp64 && p->maxit < kPlainCap;
+    auto refined = [&](int k) {
+        return fp64 && (mixed ? p->has_n[k] : nn == 256 >> k && tile_refined(nn, 1, t.cpt));
+    };
     if (!mixed) {
-        HIP_TRY(launch_solve(nn, p->desc.precision, t, a, wgs, s));
+        if (!(plain && tile_refined(nn, 1, t.cpt)))
+            HIP_TRY(launch_solve(nn, p->desc.precision, t, a, wgs, s));
     } else {
         // One launch for the 256^2 prefix of the queue (groups of four
         // workgroups) and the 128^2 items, which its workgroups take over when
@@ -362,7 +370,7 @@ int32_t enqueue_solve(rd_problem *p, int n, const double *theta, const int *grid
         // smaller and share a CU.  Each launch has a queue head of its own and
         // passes over the other sizes.
         const int prec = p->desc.precision;
-        if (p->has_n[0] || p->has_n[1]) {
+        if ((p->has_n[0] || p->has_n[1]) && !plain) {
             int big = std::min(p->n_cu, p->gws_slots) / 32 * 32;
             big = std::min(big, (n * kCoopG + 31) / 32 * 32);
             a.coop_wgs = p->has_n[0] ? std::min(big, p->group_cap * kCoopG / 32 * 32) : 0;
@@ -370,7 +378,7 @@ int32_t enqueue_solve(rd_problem *p, int n, const double *theta, const int *grid
         }
         a.coop_wgs = 0;
         for (int k = 0; k < 2; ++k) {
-            if (!p->has_n[2 + k])
+            if (!p->has_n[2 + k] || (plain && k == 0))
                 continue;
             a.queue = heads + 1 + k;
             const int most = std::min(p->n_cu * p->class_wpc[k], p->gws_slots);
@@ -378,12 +386,9 @@ int32_t enqueue_solve(rd_problem *p, int n, const double *theta, const int *grid
         }
     }
     for (int k = 0; k < 3; ++k) {
-        const int m = 256 >> k;
-        const bool refined = p->desc.precision == RD_PRECISION_FP64 &&
-                             (mixed ? p->has_n[k] : nn == m && tile_refined(nn, 1, t.cpt));
         a.queue = heads + 3 + k;
-        if (refined)
-            HIP_TRY(launch_solve_plain64(m, a, false, s));
+        if (refined(k))
+            HIP_TRY(launch_solve_plain64(256 >> k, a, plain, s));
     }
     HIP_TRY(record_solve_end(p, s, e0));
     return RD_OK;

@@ -87,6 +87,15 @@ constexpr int kGroupCpt = 32;  // its tile (cells per thread)
 size_t group_workspace_bytes(int groups);
 hipError_t launch_group_tables(void *ws, int groups, hipStream_t s);
 hipError_t launch_solve_group(int precision, SolveArgs a, int wgs, bool mixed, hipStream_t s);
+// A cap on the iterations below this asks for a bound on plain CG's work, and
+// plain CG it is: in FP32 the same kernel without its preconditioner, in FP64
+// the streamed solve.  Preconditioned solves stay below it, so that a cap
+// from here on stops none that plain CG finished within it: 40 prior draws with
+// d from 0.01 to 50, rough and smooth fields, dt from 1e-7 to 2.5e-4, take at
+// most 6 iterations at rtol 1e-9 in FP32, and in FP64, over all corrections, 8
+// at 1e-7 and 16 at 1e-14 (plain CG 4 to 725, and 8 to 1068).
+constexpr int kPlainCap = 16;
+
 // FP64 plain CG with every array in global memory, for the items of size n that
 // the preconditioned FP64 solve leaves to it (all: every item).
 hipError_t launch_solve_plain64(int n, SolveArgs a, bool all, hipStream_t s);

@@ -781,12 +781,6 @@ __device__ __forceinline__ void start(X &x, const System &y, int sp, int kn, int
         v.sbar = y.inv_dt;
 }
 
-// A cap on the iterations below this asks for a bound on plain CG's work (a
-// preconditioned iteration does the work of several): the iteration then runs
-// without the preconditioner, and solves that such a cap stops are stopped
-// as before.
-constexpr int kPlainCap = 16;
-
 // Preconditioned CG: d += A^-1 r until |r|^2 <= stop2 (r is updated
 // recursively).  Returns RD status bits; st, if it is set, before any iteration.
 template <class X>
@@ -1043,10 +1037,10 @@ __device__ __forceinline__ double fp64_rtol2(double rtol2, double floor2)
 // covers it.  Measured, relative error of u against 64 bits, 12 sets of 10
 // prior draws of 32 x 32, 446 steps, rtol 1e-7: plain CG 6.4e-7 to 2.6e-6, at
 // the caller's tolerance 1.0e-6 to 2.5e-6, at half of it 3.8e-7 to 1.2e-6; 5000
-// growing items 54.0 against 52.7 us per step.
-__device__ __forceinline__ double fp32_rtol2(double rtol2, int sp)
+// growing items 54.0 against 52.7 us per step.  (Plain CG under a cap: as asked.)
+__device__ __forceinline__ double fp32_rtol2(double rtol2, int sp, int maxit)
 {
-    return sp ? rtol2 : fmax(fmin(rtol2, 1e-16), 0.25 * rtol2);
+    return sp || maxit < kPlainCap ? rtol2 : fmax(fmin(rtol2, 1e-16), 0.25 * rtol2);
 }
 
 // Corrections of an FP64 system after its first solve: refined until the
@@ -1165,7 +1159,7 @@ __device__ __forceinline__ void solve_item(const SolveArgs &a, int c, const Grid
             v.it = 0;
             v.maxit = a.maxit;
             v.floor2 = kFp64 ? uniform(fp64_floor2(y.c * a.dt)) : 0.0;
-            v.rtol2 = kFp64 ? uniform(fp64_rtol2(a.rtol2, v.floor2)) : fp32_rtol2(a.rtol2, sp);
+            v.rtol2 = kFp64 ? uniform(fp64_rtol2(a.rtol2, v.floor2)) : fp32_rtol2(a.rtol2, sp, a.maxit);
             const int npred = (quiet >> sp) & 1 ? 0 : np;
             start(x, y, sp, kn, npred, r, sg, d, es, v, still);
             st = pcg(x, y, r, sg, d, v.rtol2 * v.bb, v, kFp64 && out_of_range<S>(y, v) ? kStRedo : 0);
