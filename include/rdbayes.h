@@ -192,18 +192,19 @@ int32_t log_likelihood_batch(rd_problem *p, int32_t n, const double *theta,
  * serving loops, harnesses that forbid it).  Same results as
  * log_likelihood_batch with grid_id = NULL (the same kernels; items are
  * independent, so the launch shape does not change any result), but the
- * solve's scratch (queue head and one workspace slot per workgroup) lives
- * in a file-scope device array of the library, 256 B + 96 MiB, one copy per
+ * solve's scratch (queue heads and one workspace slot per workgroup) lives
+ * in a file-scope device array of the library, 256 B + 128 MiB, one copy per
  * device, held until the process ends, instead of the problem's workspace.
  * The call allocates nothing (no hipMalloc, events or library routines that
- * allocate) and enqueues a fill kernel and the solve kernel on `stream`.
- * The launch uses at most as many workgroups as slots fit in the 96 MiB
- * (256 at 128 x 128 FP32, 64 at 128 x 128 FP64), so it is never wider than
- * the scratch; larger batches are served by the persistent queue.
+ * allocate) and enqueues kernels on `stream`.
+ * The launch uses at most as many workgroups as slots fit in the 128 MiB
+ * (256 at 128 x 128 FP32, 170 at 128 x 128 FP64, 32 groups of four at 256 x
+ * 256 FP64), so it is never wider than the scratch; larger batches are served
+ * by the persistent queue.
  * Every call on a device shares that device's array: calls that overlap on
  * one device (other streams, other problems, other threads) race and must
- * be serialised by the caller.  One grid class only; the cooperative
- * 256 x 256 FP32 tile is not served (select a streamed tile).
+ * be serialised by the caller.  One grid class only; the 256 x 256 FP32
+ * tiles of several workgroups are not served (select a streamed tile).
  * Errors: RD_EINVAL (n outside [0, max_batch], NULL theta/phi/status, no
  * data y), RD_EUNSUPPORTED (several grid classes, cooperative tile, a slot
  * larger than the scratch), RD_EHIP. */

@@ -64,9 +64,10 @@ long tune_key(int dev, int n, int prec)
 
 }  // namespace
 
-// Scratch of log_likelihood_batch_noalloc: the queue head (the first 256
-// bytes), then one solve slot per workgroup (predictor history and the low
-// parts of the compensated fields; streamed tiles also their strip arrays).
+// Scratch of log_likelihood_batch_noalloc: the queue heads (the first 256
+// bytes), then one solve slot per workgroup (fields and predictor history;
+// streamed tiles also their strip arrays), after the workspace of the groups
+// where FP64 256^2 items take one.
 // Every device the library runs on holds one copy until the process ends.
 // In host code `scratch` names a host-side stand-in: its device address is
 // taken once per device with hipGetSymbolAddress and used from then on.
@@ -157,8 +158,6 @@ struct rd_problem {
     int coop_wpc = 0;        // resident cooperative workgroups per CU
     void *group_ws = nullptr;  // workspace of the spectral 256^2 groups
     int group_cap = 0;
-    TileChoice noalloc_tile{};  // streamed tile of a 256^2 FP64 problem
-    int noalloc_wpc = 0;
     // cooperative waits: bound (100 MHz ticks), test-hook stall, and the
     // device count of members whose wait gave up since the last check
     unsigned long long coop_wait_ticks = 1000000000ull;
@@ -270,8 +269,8 @@ struct SolveWs {
     void *gws;
     size_t stride;
     int slots;
-    TileChoice tile;
-    int wgs_per_cu;
+    void *group_ws;  // workspace of FP64 256^2 groups (its tables not yet formed), or null
+    int group_cap;
 };
 
 int32_t enqueue_solve(rd_problem *p, int n, const double *theta, const int *grid_id,
@@ -323,15 +322,15 @@ int32_t enqueue_solve(rd_problem *p, int n, const double *theta, const int *grid
         a.gws_slots = ws->slots;
         a.coop = nullptr;
         a.coop_groups = 0;
-        a.group_ws = nullptr;
-        a.group_cap = 0;
+        a.group_ws = ws->group_ws;
+        a.group_cap = ws->group_cap;
     }
-    const TileChoice t = ws ? ws->tile : p->tile[g];
+    const TileChoice t = p->tile[g];
     // wgs_per_cu was queried when the tile was chosen: no runtime query may
     // run here, since this is also called while a stream is being captured.
-    int wgs = p->n_cu * (ws ? ws->wgs_per_cu : p->wgs_per_cu[g]);
+    int wgs = p->n_cu * p->wgs_per_cu[g];
     if (ws) {
-        if (mixed || cost || tile_coop(nn, p->desc.precision, t.cpt))
+        if (mixed || cost || (tile_coop(nn, p->desc.precision, t.cpt) && !ws->group_ws))
             return fail(RD_EUNSUPPORTED, "external workspace: single-class, uncooperative tiles only");
         wgs = std::min(wgs, ws->slots);
     }
@@ -352,6 +351,8 @@ int32_t enqueue_solve(rd_problem *p, int n, const double *theta, const int *grid
     hipEvent_t e0 = nullptr;
     if (!ws)  // (event creation may allocate: an external workspace is never timed)
         HIP_TRY(record_solve_start(p, s, &e0));
+    if (ws && ws->group_ws)
+        HIP_TRY(launch_group_tables(ws->group_ws, ws->group_cap, s));
     unsigned *const heads = a.queue;
     // FP64 sizes solved by FP32 corrections: plain CG takes what those leave,
     // and everything under a small iteration cap
@@ -630,10 +631,6 @@ extern "C" int32_t init_problem(const rd_problem_desc *desc, rd_problem **out)
         p->tile[g] = TileChoice{cpt, nn / cpt};
         p->wgs_per_cu[g] = solve_wgs_per_cu(gd.n, desc->precision, cpt);
     }
-    if (desc->precision == RD_PRECISION_FP64 && desc->n_grids == 1 && max_n == 256) {
-        p->noalloc_tile = TileChoice{128, 256 * 256 / 128};
-        p->noalloc_wpc = solve_wgs_per_cu(256, desc->precision, 128);
-    }
     p->maxit = desc->cg_maxit > 0 ? desc->cg_maxit : 10 * max_n * max_n;
     p->max_n = max_n;
     const int B = desc->max_batch;
@@ -825,27 +822,36 @@ extern "C" int32_t log_likelihood_batch_noalloc(rd_problem *p, int32_t n, const 
     if (!p->grids_host[0].y)
         return fail(RD_EINVAL, "grid 0 has no data y");
     const int nn = p->grids_host[0].n;
-    // (the default 256^2 tile in FP64 needs the group workspace: the streamed
-    // one takes its place)
-    const bool streamed = p->noalloc_wpc && tile_coop(nn, p->desc.precision, p->tile[0].cpt);
-    const TileChoice t = streamed ? p->noalloc_tile : p->tile[0];
-    if (tile_coop(nn, p->desc.precision, t.cpt))
+    const TileChoice t = p->tile[0];
+    const bool group = tile_refined(nn, p->desc.precision, t.cpt) &&
+                       tile_coop(nn, p->desc.precision, t.cpt);
+    if (tile_coop(nn, p->desc.precision, t.cpt) && !group)
         return fail(RD_EUNSUPPORTED,
                     "log_likelihood_batch_noalloc: the cooperative %dx%d tile needs the problem's "
                     "group workspace (select a streamed tile with rd_set_tile)", nn, nn);
     if (!p->scratch)
         return fail(RD_EHIP, "no scratch address for device %d", p->device);
     const size_t stride = (solve_slot_bytes(nn, p->desc.precision, t.cpt) + 255) / 256 * 256;
-    const size_t slots = kNoAllocSlots / stride;
+    // FP64 256^2: as many groups (in whole blocks of eight) as fit with their
+    // workspace and a slot for each of their workgroups
+    int groups = 0;
+    size_t area = 0;
+    if (group) {
+        auto room = [](int g) { return (group_workspace_bytes(g) + 255) / 256 * 256; };
+        while (room(groups + 8) + (size_t)(groups + 8) * kCoopG * stride <= kNoAllocSlots)
+            groups += 8;
+        area = room(groups);
+    }
+    const size_t slots = group ? (size_t)groups * kCoopG : kNoAllocSlots / stride;
     if (slots < 1)
         return fail(RD_EUNSUPPORTED,
                     "log_likelihood_batch_noalloc: one solve slot (%zu bytes) exceeds the %zu "
                     "bytes of scratch", stride, kNoAllocSlots);
     if (n == 0)
         return RD_OK;
-    SolveWs ws{(unsigned *)p->scratch, (char *)p->scratch + kNoAllocHeader, stride,
-               (int)std::min<size_t>(slots, (size_t)1 << 20), t,
-               streamed ? p->noalloc_wpc : p->wgs_per_cu[0]};
+    char *const base = (char *)p->scratch + kNoAllocHeader;
+    SolveWs ws{(unsigned *)p->scratch, base + area, stride,
+               (int)std::min<size_t>(slots, (size_t)1 << 20), group ? base : nullptr, groups};
     return enqueue_solve(p, n, theta, nullptr, nullptr, phi, status, cg_iters, nullptr, nullptr,
                          (hipStream_t)stream, 0, nullptr, nullptr, &ws);
 }
