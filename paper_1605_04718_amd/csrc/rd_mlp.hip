@@ -307,20 +307,21 @@ static hipError_t gemm(const GemmArgs &g, hipStream_t s)
 // First layer (fan-in 4): x = 2 (phi - lo) / (hi - lo) - 1 (zero in padded
 // rows), z = x W^T + b, h = GELU(z).  A block takes 16 rows and 64 columns; a
 // thread four rows of one column.  z, x and ht are written in training only.
+// (Rows on the grid's x: its y ends at 65535 blocks, a million rows of 16.)
 template <bool kTrain>
 __global__ __launch_bounds__(256) void k_layer0(int n, int width, const double *phi, SurScale sc,
                                                 const float *W, const float *b, float *x0,
                                                 float *z, bf16 *h, bf16 *ht, int ldt)
 {
     __shared__ float xs[16][4];
-    const int t = threadIdx.x, m0 = blockIdx.y * 16, col = blockIdx.x * 64 + (t & 63);
+    const int t = threadIdx.x, m0 = blockIdx.x * 16, col = blockIdx.y * 64 + (t & 63);
     if (t < 64) {
         const int r = m0 + (t >> 2), c = t & 3;
         const float v =
             r < n ? (float)(2.0 * (phi[4 * (size_t)r + c] - sc.lo[c]) / (sc.hi[c] - sc.lo[c]) - 1.0)
                   : 0.0f;
         xs[t >> 2][c] = v;
-        if (kTrain && blockIdx.x == 0)
+        if (kTrain && blockIdx.y == 0)
             x0[4 * (size_t)r + c] = v;
     }
     __syncthreads();
@@ -750,7 +751,7 @@ static hipError_t forward(Surrogate *s, int rows, const double *phi, hipStream_t
         sc.lo[i] = s->d.lo[i];
         sc.hi[i] = s->d.hi[i];
     }
-    hipLaunchKernelGGL(k_layer0<kTrain>, dim3(s->dout[0] / 64, mp / 16), dim3(256), 0, st, rows,
+    hipLaunchKernelGGL(k_layer0<kTrain>, dim3(mp / 16, s->dout[0] / 64), dim3(256), 0, st, rows,
                        s->dout[0], phi, sc, s->W[0], s->b[0], s->x0, s->Z[0], s->H[0], s->Ht[0],
                        s->bpad);
     hipError_t e = hipGetLastError();
