@@ -14,9 +14,6 @@
 // cyclic reduction over all rows takes 16 per row, system and each of its six
 // levels and an LDS round trip with a barrier per level.  The fields stay in
 // registers for the whole horizon; only the data and the results touch HBM.
-// Error of u against long double, r.m.s. of 128 items after 1000 steps, n = 20 /
-// 64 / 100 / 128: 4.7e-14, 3.7e-14, 4.2e-14, 4.5e-14; cyclic reduction 6.0e-14,
-// 4.9e-14, 4.9e-14, 5.8e-14.
 //
 // What bounds it: FP64 issue, with one wavefront per SIMD at 4096 items.
 // Measured, n = 100, 1000 steps of 4096 items: 1.21 ms; cyclic reduction over
@@ -40,7 +37,7 @@ constexpr int kLanes = 16;  // lanes of an item (a DPP row)
 
 struct Args {
     int n, n_steps, law, obs;
-    double inv_tau, tau, T, inv_T, rho_T;
+    double inv_tau, tau, inv_T, rho_T;
     double a, b, g, d;
     double inv_2s2;           // 1 / (2 sigma^2)
     const double *u0, *v0;    // [n]
@@ -67,22 +64,15 @@ __device__ inline double recip(double x)
     return fma(r, e, r);
 }
 
-// n / d to an ulp from a reciprocal r of d.
-__device__ inline double quotient(double n, double d, double r)
-{
-    const double q = n * r;
-    return fma(fma(-d, q, n), r, q);
-}
-
 // rho(t) and rho'(t).  Polynomial: Horner in s = t / T with beta_4 fixed by
 // rho(T) = rho_T; the data laws of eq. (grates).
 __device__ inline void growth(const Args &a, double b1, double b2, double b3, double b4, double t,
                               double &rho, double &drho)
 {
     if (a.law == G1D_LAW_POLY) {
-        const double s = quotient(t, a.T, a.inv_T);
+        const double s = t * a.inv_T;
         rho = 1.0 + s * (b1 + s * (b2 + s * (b3 + s * b4)));
-        drho = quotient(b1 + s * (2.0 * b2 + s * (3.0 * b3 + s * 4.0 * b4)), a.T, a.inv_T);
+        drho = (b1 + s * (2.0 * b2 + s * (3.0 * b3 + s * 4.0 * b4))) * a.inv_T;
     } else if (a.law == G1D_LAW_EXP) {
         rho = exp(0.001 * t);
         drho = 0.001 * rho;
@@ -137,9 +127,19 @@ __device__ __forceinline__ double item_sum(double x)
     return x;
 }
 
+// The pivots of the forward pass.  kExcess: as the pivot less the coupling to
+// the next row, e, which is what stays of the diagonal when the neighbours'
+// couplings are taken out: the row's own excess and the part of the previous
+// row's, all positive, where b - c^2 / b of the full diagonals cancels it out of
+// 2 k.  From five rows a lane that cancellation shows (r.m.s. error of u against
+// long double, 1000 steps, n = 100 / 128: full diagonals 5.8e-14 / 7.7e-14, this
+// 4.0e-14 / 4.3e-14, cyclic reduction over all rows 4.9e-14 / 5.8e-14); below, full
+// diagonals are no further off than cyclic reduction (n = 64: 4.5e-14 for 4.9e-14),
+// and this takes 4 to 7 % longer at n = 48 and 64.
 template <int M>
 __global__ __launch_bounds__(64) void k_g1d_solve(Args a)
 {
+    constexpr bool kExcess = M > 4;
     const int lane = threadIdx.x & (kLanes - 1), sub = threadIdx.x / kLanes;
     const int item = blockIdx.x * (64 / kLanes) + sub;
     const int n = a.n, i0 = lane * M;
@@ -178,9 +178,9 @@ __global__ __launch_bounds__(64) void k_g1d_solve(Args a)
                 st = RD_ST_OUT_OF_PRIOR;
             } else {
                 const double rr = recip(rho);
-                const double base = quotient(drho, rho, rr) + a.inv_tau;
+                const double base = fma(drho, rr, a.inv_tau);
                 double kk[2];
-                kk[0] = quotient(quotient(nn, rho, rr), rho, rr);
+                kk[0] = nn * rr * rr;
                 kk[1] = a.d * kk[0];
                 // rows after the forward pass: x_j = dr + fr x_left + cr x_{j+1}
                 double cr[2][M], dr[2][M], fr[2][M], c[2], b[2], d[2], f[2], e[2];
@@ -195,22 +195,20 @@ __global__ __launch_bounds__(64) void k_g1d_solve(Args a)
 #pragma unroll
                     for (int s = 0; s < 2; ++s) {
                         dj[s] = fma(x[s][j], a.inv_tau, src[s][j]);
-                        // The pivot less the coupling to the next row, e: what
-                        // stays of the diagonal when the neighbours' couplings
-                        // are taken out, the row's own excess and the part of
-                        // the previous row's, all positive; b - c^2 / b of the
-                        // full diagonals would cancel it out of 2 k.
-                        if constexpr (M == 1)
-                            bj[s] = fma(kk[s], nb[j], bj[s]);
-                        else
+                        if constexpr (kExcess) {
                             bj[s] = j > 0 ? fma(cr[s][j - 1], e[s], bj[s]) : bj[s] + f[s];
+                        } else {
+                            bj[s] = fma(kk[s], nb[j], bj[s]);
+                            if (j > 0)
+                                bj[s] = fma(-c[s], cr[s][j - 1], bj[s]);
+                        }
                         if (j > 0) {  // c: coupling of row j - 1 to this one
                             dj[s] = fma(c[s], dr[s][j - 1], dj[s]);
                             f[s] = c[s] * fr[s][j - 1];
                         }
                         c[s] = kk[s] * cpl[j];
                         e[s] = bj[s];
-                        if constexpr (M > 1)
+                        if constexpr (kExcess)
                             bj[s] += c[s];
                         if (j < M - 1) {
                             const double rb = recip(bj[s]);
@@ -368,8 +366,7 @@ g1d::Args base_args(const g1d_problem *p)
     a.obs = d.obs;
     a.tau = d.tau;
     a.inv_tau = 1.0 / d.tau;
-    a.T = (double)d.n_steps * d.tau;
-    a.inv_T = 1.0 / a.T;
+    a.inv_T = 1.0 / ((double)d.n_steps * d.tau);
     a.rho_T = d.rho_T;
     a.a = d.theta[0];
     a.b = d.theta[1];
