@@ -393,7 +393,9 @@ int32_t surrogate_params(rd_problem *p, int32_t layer, float *w, float *b, int32
 /* Re-runs the tile-shape autotuner for every grid class of p (a few timed
  * trial solves) and keeps the fastest; returns the chosen cells-per-thread
  * of each class in cpt_out (host int32 [n_grids], may be NULL).  The choice
- * is cached per device, grid size and precision for later problems. */
+ * is cached per device, grid size and precision for later problems.  Below
+ * 256 x 256 every tile of a precision is the same kernel: no solve is timed
+ * and the present one stays. */
 int32_t rd_autotune(rd_problem *p, int32_t *cpt_out);
 
 /* Selects the tile of grid class `grid` by its cells per thread (the value

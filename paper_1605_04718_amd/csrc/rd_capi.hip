@@ -1142,6 +1142,8 @@ extern "C" int32_t rd_autotune(rd_problem *p, int32_t *cpt_out)
         int best = p->tile[g].cpt;
         float best_ms = 1e30f;
         for (int cpt : {4, 8, 16, 32, 64, 128}) {
+            if (n < 256)  // one kernel whatever the tile: the incumbent stays
+                break;
             const bool coop = tile_coop(n, p->desc.precision, cpt);
             if (!tile_supported(n, p->desc.precision, cpt) ||
                 (!coop && (n * n / cpt > 1024 || n * n / cpt < 64)))
