@@ -4,7 +4,8 @@ and with a surrogate first stage (delayed acceptance).
 One step = one Metropolis step (Algorithm 1) of every chain: proposal, fused
 IMEX/CG forward solve + Gaussian misfit of every in-box proposal,
 accept/reject.  Workload (the batched plain-sampler configuration): 4096
-chains, 128 x 128 cells, FP32 fields with FP64 reductions, four free
+chains, 128 x 128 cells, FP32 problem (FP64 fields in the solve, FP32
+increments, FP64 reductions), four free
 parameters (a, b, ln gamma, ln d) with a uniform prior box a, b in [0, 1],
 gamma in [50, 500], d in [5, 50] (log-uniform), proposal s.d. 2 % of each
 box side, T = 2, synthetic data from theta = (0.1, 0.9, 200, 10) with 1 %
@@ -87,25 +88,25 @@ PEAK_FP64 = 78.6e12    # MI355X vector FP64; FLOP/s
 FLOP_CG_ITER = 20.0
 FLOP_SETUP = 21.0
 FLOP_MISFIT = 3.0
-# Work the FP32 kernel issues beyond that (per cell, per species): the
-# residual of the low part of the compensated field (12), the compensated
-# fold (9 more than x += d), the predictor sweep (A H 10, two dot products
-# 4, d0 = w H 1, r -= w A H 2 -> 17; skipped after a step without CG
-# iterations, so counted as an upper bound) per step, and the diagonal
-# re-formed in each CG iteration (3).
-FLOP_OVERHEAD_STEP = 12.0 + 9.0 + 17.0
-FLOP_OVERHEAD_ITER = 3.0
-# HBM bytes of the fused solve kernel from two rocprofv3 PMC passes over the
-# timed step of `bench.py --steps 1 --warmup 0 --no-da --no-cpu-baseline
-# --no-mixed --no-stationary --no-config1 --no-loglik-error --legacy-steps 0`
-# at CG rtol 1e-9 (3831 solves, 29 438 831 completed solve-steps): FETCH_SIZE
-# 4 816 000 000 KiB x 2.00 + WRITE_SIZE 7 476 000 000 KiB x 1.00 (factors from a
-# 256 MiB copy), per completed solve-step.  Valid only for the kernel version
-# and tile it was measured on (step residual in FP64 below rtol 3e-8,
-# two-increment CG start, own-cell LDS and history reads grouped by four,
-# row-summed workgroup reductions, 112 B scratch per lane; the queue order does
-# not change what a solve reads or writes).
-MEASURED_TRAFFIC = {"k_solve_resident<128,16,float>": 595084.5}
+# Work the FP32 kernel issues beyond that (per cell, per species): the start
+# vector from two increments per step (A h1 and A h2 20, five dot products 10,
+# d0 3, its residual 11, its norm 2; skipped for a system at rest, so an upper
+# bound) and the product r.z per iteration (2).  The preconditioner's four
+# transforms on the matrix cores come on top (8 N per application).
+FLOP_OVERHEAD_STEP = 46.0
+FLOP_OVERHEAD_ITER = 2.0
+# Bytes past the L2s of the fused solve kernel from two rocprofv3 PMC passes
+# over the timed step of `bench.py --steps 1 --warmup 0 --no-da
+# --no-cpu-baseline --no-mixed --no-stationary --no-config1
+# --no-loglik-error --legacy-steps 0` at CG rtol 1e-9 (3831 solves, 29 438 832
+# completed solve-steps): FETCH_SIZE 8 434 455 372 KiB x 2.00 + WRITE_SIZE
+# 3 192 108 758 KiB x 1.00 (factors from a 256 MiB copy), per completed
+# solve-step.  The 256 slots (128 MiB) are served by the memory-side cache.
+# Valid only for the kernel version it was measured on (the queue order does
+# not change what a solve reads or writes); the second entry is the plain-CG
+# kernel that served this size before, for comparison with earlier runs.
+MEASURED_TRAFFIC = {"k_solve_pcg<S128,float>": 697802.0,
+                    "k_solve_resident<128,16,float>": 595084.5}
 STATUS_BITS = ["not_converged", "breakdown", "nonfinite", "out_of_prior", "bad_grid",
                "not_steady", "group_timeout", "bit7"]
 GOLDEN = os.path.join(ROOT, "tests", "golden", "loglik_64.npz")
@@ -623,9 +624,9 @@ def config1_oracle(log):
 def mixed_leg(args, log):
     """The uneven workload: chains split 4:2:1 over 64^2, 128^2 and 256^2
     grids, half on stationary and half on growing domains (rho = e^{0.01 t}),
-    six datasets; per step one launch (1024-thread workgroups: groups of four
-    solve the 256^2 items, then join the other classes) or two (512: a
-    cooperative launch, then the mixed one), replayed from a captured graph;
+    six datasets; per step one launch for the 256^2 items (groups of four
+    workgroups) and the 128^2 ones and one for the 64^2 items, replayed from a
+    captured graph;
     wall-clock cell-steps/s of the solves performed."""
     import torch
     from paper_1605_04718_amd import inputs
@@ -665,7 +666,7 @@ def mixed_leg(args, log):
                 max_batch=C)
     p.autotune()
     T = p.mixed_threads()
-    log(f"mixed: autotuned workgroup {T} threads; initial misfits of {C} chains")
+    log(f"mixed: initial misfits of {C} chains")
     phi0 = inputs.box_draws(C, LO, HI, seed=inputs.SEED_CHAIN_INIT)
     ll0, st0, _ = p.log_likelihood(torch.tensor(inputs.to_natural(phi0), device="cuda"),
                                    grid_id=ids)
@@ -708,15 +709,13 @@ def mixed_leg(args, log):
         per_fail[name] = fail_dict(fails[idn == k].sum(0))
         cell_steps += float(done[idn == k].sum()) * n * n
     p.close()
-    log(f"mixed: {C} chains, workgroup {T} threads, {args.mixed_steps} steps in {wall:.2f} s")
+    log(f"mixed: {C} chains, {args.mixed_steps} steps in {wall:.2f} s")
     return {"workload": f"{C} chains: {counts[64]} x 64^2, {counts[128]} x 128^2, "
                         f"{counts[256]} x 256^2 (the 4:2:1 mix at {args.mixed_scale:g} of 4095 "
                         "chains), half stationary and half growing (rho = exp(0.01 t)), 6 datasets, "
-                        "T=2, " + ("one launch per step (256^2 items by groups of four "
-                                   "workgroups, then the other classes)" if T == 1024 else
-                                   "per step a cooperative launch for the 256^2 items and a "
-                                   "persistent launch for the rest") +
-                        ", replayed from a captured graph",
+                        "T=2, per step one launch for the 256^2 items (groups of four "
+                        "workgroups) and the 128^2 ones and one for the 64^2 items, "
+                        "replayed from a captured graph",
             "cell_steps_per_s": cell_steps / wall, "ms_per_step": 1e3 * wall / args.mixed_steps,
             "steps": args.mixed_steps, "cell_steps_note": "IMEX steps the solves completed",
             "mixed_threads": T, "solves_per_class": per, "cg_maxit": CG_MAXIT_MIXED,
@@ -726,7 +725,7 @@ def mixed_leg(args, log):
 
 def precision_256_leg(args, log):
     """FP32 at 256^2 against the FP64 oracle: 16 prior draws solved to T = 2
-    on the stationary domain by the FP32 path (cooperative tile) at CG rtol
+    on the stationary domain by the FP32 path (groups of workgroups) at CG rtol
     1e-7 and at the timed legs' tolerance; relative L2 of the final u and v
     fields against the oracle's fields at rtol 1e-10
     (tests/golden/precision_256.npz).  Beside each draw: the oracle's own
@@ -753,7 +752,7 @@ def precision_256_leg(args, log):
         return float(np.linalg.norm(a - b) / np.linalg.norm(b))
 
     out = {"workload": f"{m} prior draws, 256x256, stationary, T=2 ({n_steps} steps of "
-                       "2.5e-4), FP32 path (compensated fields, cooperative tile) against the "
+                       "2.5e-4), FP32 path (groups of four workgroups) against the "
                        "FP64 oracle at CG rtol 1e-10",
            "oracle_rtol_1e-7_vs_1e-10": [float(x) for x in gold["cg_sensitivity"]],
            "oracle_amplification_of_6e-8": [float(x) for x in gold["amplification"]]}
@@ -792,9 +791,9 @@ def growth1d_leg(args, log):
     timed horizon is shorter and the full-horizon time is extrapolated).
     Data: the exponential-growth solution of the same horizon plus 5 %
     noise.  FLOPs are the kernel's issued float64 operations (a reciprocal
-    counted as one): per padded row and reduction level 14, per row and
-    step 13 more for assembly and the final solve; 128 rows x 2 systems,
-    6 exchange levels at n = 100 (the seventh is a lane-local 2 x 2 solve)."""
+    counted as one): in each of 16 lanes and for both systems, 24 per row
+    (assembly, elimination, substitution), 14 per level of the four of cyclic
+    reduction and 8 for the lane's closing row."""
     import torch
     from paper_1605_04718_amd import inputs
     from paper_1605_04718_amd.api import Growth1D
@@ -820,8 +819,7 @@ def growth1d_leg(args, log):
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1)
     g.close()
-    levels = 6 if n > 64 else math.ceil(math.log2(n))
-    flops = m * steps * 2 * 128 * (14 * levels + 13)
+    flops = m * steps * 2 * 16 * (24 * math.ceil(n / 16) + 14 * 4 + 8)
     achieved = flops / (ms * 1e-3)
     full_steps = int(round(600 / tau))
     log(f"growth1d: {m} items x {steps} steps in {ms:.1f} ms")
@@ -960,7 +958,7 @@ def main():
     p = Problem([Grid(n=N_CELLS, u0=u0, v0=v0, y=y, sigma=sigma)], TAU, n_steps, CG_RTOL,
                 cg_maxit=CG_MAXIT, lo=LO, hi=HI, step=step, max_batch=C)
     cpt = p.autotune()[0]
-    log(f"autotuned tile: {cpt} cells per thread ({N_CELLS * N_CELLS // cpt} threads)")
+    log(f"tile: {cpt} cells per thread")
     phi0 = inputs.box_draws(C, LO, HI, seed=inputs.SEED_CHAIN_INIT)
     phi0_t = torch.tensor(phi0, dtype=torch.float64, device=dev)
     th0 = torch.tensor(inputs.to_natural(phi0), dtype=torch.float64, device=dev)
@@ -1004,7 +1002,8 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32 fields (compensated hi+lo) and CG vectors; f64 dots, misfit, accept",
+        "dtype": "f32 CG vectors and operator (f16 matrix-core preconditioner); f64 fields, "
+                 "residuals, dots, misfit, accept",
         "data": f"synthetic: {data_src}",
         "config": {"workload": "batched plain sampler: 4096 chains, 128x128, T=2 (dt 2.5e-4, 8000 "
                                "IMEX steps), 4 params, step 2% of prior range, chains from prior "
@@ -1026,8 +1025,9 @@ def main():
         "roofline": {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_FP32 / 1e12,
                      "unit": "TFLOP/s", "frac": achieved / PEAK_FP32,
                      "traffic": traffic_per_launch,
-                     "traffic_unit": "bytes per launch (PMC FETCH_SIZE + WRITE_SIZE, scaled by "
-                                     "the measured per-solve-step figure of this kernel)",
+                     "traffic_unit": "bytes per launch past the L2s, from the memory-side cache "
+                                     "(PMC FETCH_SIZE x 2 + WRITE_SIZE per solve-step of this "
+                                     "kernel, times the solve-steps)",
                      "kernel": kernel,
                      "kernel_ms_per_launch": kern_ms / launches,
                      "launches": plain["launches"],
@@ -1043,9 +1043,9 @@ def main():
                                  "the matrix cores) are not counted",
                      "frac_of_nonpacked_fp32": achieved / PEAK_FP32_NONPACKED,
                      "overhead_flops_per_launch_upper": overhead / launches,
-                     "overhead_note": "compensated low part, compensated fold, predictor sweep "
-                                      "and the re-formed diagonal: issued, not counted in "
-                                      "achieved"},
+                     "overhead_note": "start vector from two increments and the product r.z: "
+                                      "issued, not counted in achieved (the preconditioner's "
+                                      "transforms come on top, on the matrix cores)"},
     }
 
     if not args.no_da:

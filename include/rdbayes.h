@@ -20,8 +20,10 @@
  * linearisation
  *   [1/dt + 2 r + g (1 - u^n v^n)] u^{n+1} - rho_n^-2 Lap_h u^{n+1} = u^n/dt + g a
  *   [1/dt + 2 r + g (u^n)^2]       v^{n+1} - d rho_n^-2 Lap_h v^{n+1} = v^n/dt + g b
- * (g = gamma; both systems solved by unpreconditioned conjugate gradients,
- * stopping when ||r||_2 <= cg_rtol ||rhs||_2 on the recursive residual).
+ * (g = gamma; both systems solved by conjugate gradients, preconditioned with
+ * the constant-coefficient mean operator except where rd_problem_desc says
+ * plain, stopping when ||r||_2 <= cg_rtol ||rhs||_2 or before, see precision
+ * there).
  *
  * Conventions for every entry point:
  *  - Return value: RD_OK (0) or a negative call error (RD_E*).  A call
@@ -100,12 +102,29 @@ typedef struct {
     double dt;                     /* time step tau */
     int32_t n_steps;               /* T = dt * n_steps */
     double cg_rtol;                /* CG stop: ||r|| <= cg_rtol ||rhs|| */
-    int32_t cg_maxit;              /* CG iteration cap per solve (<= 0: 10 n^2); below 16 the
-                                    * iterations run without the preconditioner */
-    int32_t precision;             /* RD_PRECISION_FP32: fields (as hi + lo) and CG
-                                      vectors in FP32, the CG step lengths in
-                                      FP32 from FP64 dot products, Phi in FP64.
-                                      RD_PRECISION_FP64: everything FP64 */
+    int32_t cg_maxit;              /* CG iteration cap per system and step (<= 0: 10 n^2);
+                                      below 16 it bounds plain CG's iterations (a
+                                      preconditioned one does the work of several),
+                                      from 16 on the preconditioned ones, in FP64 over
+                                      all corrections of the system */
+    int32_t precision;             /* RD_PRECISION_FP32: FP32 outputs; increments, CG
+                                      vectors and operator in FP32, fields,
+                                      residuals, dot products and Phi in FP64 (the
+                                      plain-CG tiles of 256 x 256: fields as FP32
+                                      hi + lo).
+                                      RD_PRECISION_FP64: FP64 outputs, fields,
+                                      residuals, dot products and Phi.  At 32 x 32,
+                                      on the streamed tile, below cg_maxit 16 and
+                                      for systems out of the range of FP32 (fields
+                                      beyond 1e+-12, 8 c dt beyond 2^24 with c = d
+                                      n^2 / rho^2) CG is FP64 too.  Elsewhere each
+                                      system is solved by corrections from FP32 CG,
+                                      repeated until the residual evaluated in FP64
+                                      meets a twentieth of cg_rtol or its own
+                                      rounding.
+                                      In both, the preconditioner's products are FP16
+                                      on the matrix cores; it steers CG's search
+                                      directions only. */
     uint32_t free_mask;            /* bit i set: sampling coordinate i moves */
     double lo[4], hi[4];           /* uniform prior box in sampling coordinates */
     double step[4];                /* random-walk proposal s.d. per coordinate */
@@ -142,9 +161,9 @@ enum { RD_PRIOR_UNIFORM = 0, RD_PRIOR_NORMAL = 1 };
 
 /* Creates a problem: validates the description, uploads the initial fields
  * and data, sizes the workspace for max_batch items and picks the solver
- * tile shape for each grid class (autotuned once per device and grid class,
- * see rd_autotune).  Synchronous.  Errors: RD_EINVAL, RD_EHIP, RD_ENOMEM,
- * RD_EUNSUPPORTED (grid size without a kernel, FP64 at n = 256 resident). */
+ * tile shape for each grid class (the default or the choice of an earlier
+ * rd_autotune).  Synchronous.  Errors: RD_EINVAL, RD_EHIP, RD_ENOMEM,
+ * RD_EUNSUPPORTED (grid size without a kernel). */
 int32_t init_problem(const rd_problem_desc *desc, rd_problem **out);
 
 /* Releases the workspace (synchronises the device first).  NULL is a no-op. */
@@ -161,8 +180,9 @@ int32_t forward_solve_steady_batch(rd_problem *p, int32_t n, const double *theta
  * each from the initial fields of its grid class to T.
  *   theta    dev float64 [n][4] natural parameters (a, b, gamma, d)
  *   grid_id  dev int32 [n] grid class of each item, or NULL (class 0).
- *            With several classes the batch runs as one persistent launch
- *            over all classes, largest grids first; an id outside
+ *            With several classes the batch runs, largest grids first, as
+ *            one persistent launch for the 256 x 256 and 128 x 128 items and
+ *            one for each smaller size; an id outside
  *            [0, n_grids) marks the item RD_ST_BAD_GRID (not solved).
  *   u_out    dev [n][M*M] final u (float32 for FP32 problems, float64 for
  *            FP64 problems), M = the largest grid size of the problem; item
@@ -438,8 +458,8 @@ int32_t rd_set_da_substeps(rd_problem *p, int32_t substeps);
  * Errors: RD_EINVAL. */
 int32_t rd_captured_graphs(const rd_problem *p, int32_t *count);
 
-/* Workgroup size of the launch that serves batches mixing grid classes
- * (host int32 out).  Errors: RD_EINVAL (NULL argument). */
+/* The value of rd_set_mixed_threads, 1024 by default (host int32 out).
+ * Errors: RD_EINVAL (NULL argument). */
 int32_t rd_mixed_threads(const rd_problem *p, int32_t *threads);
 
 /* Accumulated device time (ms, measured with HIP events on the launch
@@ -448,8 +468,8 @@ int32_t rd_mixed_threads(const rd_problem *p, int32_t *threads);
 int32_t rd_solver_timing(rd_problem *p, int32_t enable, double *ms_total, int64_t *launches,
                          int32_t reset);
 
-/* Synchronises the device and reports whether any cooperative workgroup
- * (the 256 x 256 FP32 tile, alone or inside a mixed batch) gave up a bounded
+/* Synchronises the device and reports whether any workgroup of a group that
+ * shares an item (256 x 256, alone or inside a mixed batch) gave up a bounded
  * group wait since the problem was created or last reset.  Such a wait ends
  * after 10 s only when a member of the group can never arrive (not while
  * every member is resident, which the launch guarantees); its items carry

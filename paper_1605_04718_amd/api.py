@@ -308,7 +308,8 @@ class Problem:
         check(lib().rd_set_tile(self.h, int(grid), int(cpt)), "rd_set_tile")
 
     def set_mixed_threads(self, threads):
-        """Workgroup size (512 or 1024) of the launch for batches mixing classes."""
+        """Nominal workgroup size (512 or 1024) of batches mixing classes; both
+        launch the same kernels."""
         check(lib().rd_set_mixed_threads(self.h, int(threads)), "rd_set_mixed_threads")
 
     def set_da_substeps(self, substeps):

@@ -673,8 +673,8 @@ extern "C" int32_t init_problem(const rd_problem_desc *desc, rd_problem **out)
         return fail(RD_EHIP, "upload of grid table failed");
     }
     // Solve workspace: one slot per resident workgroup, sized for every tile
-    // the autotuner may pick (low parts and predictor history, 4 n^2 values,
-    // and for streamed tiles the 6 strip arrays as well).
+    // the autotuner may pick (fields and predictor history, and for streamed
+    // tiles the strip arrays as well).
     size_t slot = 0;
     int slots = 0;
     for (int g = 0; g < desc->n_grids; ++g) {

@@ -21,7 +21,9 @@
 // add it to an FP64 field, evaluate the residual of the implicit system for
 // that field in FP64, and solve for a further correction until that true
 // residual meets the tolerance (iterative refinement; the tolerance then
-// bounds the evaluated residual, not a recursively updated one).
+// bounds the evaluated residual, not a recursively updated one).  FP64 items
+// that leave the range of FP32 corrections are left to plain CG in FP64
+// (out_of_range).
 //
 // Layout: strip s of an item is K whole rows, lane l of it the C columns
 // C l .. C l + C - 1 (R = K C cells per thread).  A wave is one strip, at
@@ -32,12 +34,15 @@
 // Global slot of a workgroup: the fields X_u, X_v in FP64, then the last two
 // increments of each species in FP32.
 //
-// What bounds it: issue of vector instructions (128 x 128: 2 000 per wave for
-// the set-up of a system, 1 800 per iteration, two waves per SIMD), and with
-// every CU busy also the passes over the slot (1.15 MB per IMEX step from L2
-// and the memory-side cache, 7 TB/s over the chip).  512 items of 128 x 128
-// near the posterior, 500 steps: 42.8 ms, plain CG 89.5; 64 FP64 items, 40
-// steps: 4.3 ms, plain CG with streamed arrays 144.
+// What bounds it, from counters: at 32 x 32 and 64 x 64 the issue of vector
+// instructions (active in 0.95 and 0.82 of the SIMDs' cycles).  At 128 x 128,
+// with every CU busy, the passes over the slots: 1.19 MB per IMEX step from the
+// memory-side cache, 7.1 TB/s over the chip, where a kernel that only walks 256
+// such slots, half of them written, gets 8.2 (vector instructions, 2 000 per
+// wave for the set-up of a system and 1 800 per iteration, 0.53); an item alone,
+// or the 64 of an FP64 batch, the latency of its passes.  512 items of 128 x 128
+// near the posterior, 500 steps: 43.2 ms, plain CG 89.5; 64 FP64 items, 40
+// steps: 4.38 ms, plain CG with streamed arrays 144.
 #pragma once
 
 namespace rd {

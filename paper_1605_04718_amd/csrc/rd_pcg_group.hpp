@@ -12,11 +12,12 @@
 // (128 KB each) come from L2.
 //
 // What bounds it: five group exchanges per iteration and three per set-up of
-// a system (a round trip between workgroups of one XCD is about 1 us), and as
-// in one workgroup the issue of vector instructions.  37 growing items, 60
-// steps: 6.6 ms (110 us per step); plain CG by a group of four 1024-thread
-// workgroups, 120 iterations a step, 41.6 ms.  The 511 items of the uneven
-// batch, 60 steps: 17.1 against 122 ms.  Twelve FP64 items: plain CG streamed
+// a system (a round trip between workgroups of one XCD is about 1 us): vector
+// instructions are active in 0.29 of the cycles of its CUs, and its waves wait
+// in 0.63 of theirs.  37 growing items, 60 steps: 6.5 ms (109 us per step);
+// plain CG by a group of four 1024-thread workgroups, 120 iterations a step,
+// 41.6 ms.  The 511 items of the uneven batch, 60 steps: 16.8 against 122 ms.
+// Twelve FP64 items: plain CG streamed
 // by one workgroup each took up to a hundred times as long.
 #pragma once
 

@@ -1875,11 +1875,15 @@ bool tile_supported(int n, int precision, int cpt)
 
 // Defaults measured on MI355X.  The spectrally preconditioned kernel
 // (rd_pcg.hpp) against plain CG: 512 items of 128^2 in FP32 near the posterior,
-// first 500 steps, 42.8 against 89.5 ms; 4096 prior draws, first 200 steps, 150
+// first 500 steps, 43.2 against 89.5 ms; 4096 prior draws, first 200 steps, 148
 // against 625 ms (51 CG iterations per step against 3); one item 36 against 111 us
-// per step; 2000 prior draws of 64^2 25.7 against 68 ms; 5000 growing items of
-// 32^2 15.0 against 20.4 ms; 64 items of 128^2 in FP64 4.3 against 144 ms; 37
-// items of 256^2 by groups of four workgroups 6.6 against 41.6 ms.
+// per step; 2000 prior draws of 64^2 25.8 against 68 ms; 5000 growing items of
+// 32^2 15.5 against 20.4 ms; 64 items of 128^2 in FP64 4.4 against 144 ms; 37
+// items of 256^2 by groups of four workgroups 6.5 against 41.6 ms.  Plain CG was
+// better for thousands of 32^2 items near rest at loose tolerances, where the
+// set-up is what a step costs (2000 items, 1500 steps: rtol 1e-7 19.8 against
+// 21.3 us per step, 1e-5 9.4 against 11.3), which nothing tells beforehand from a
+// batch in its transient.
 int default_cpt(int n, int precision)
 {
     if (precision == 0)
